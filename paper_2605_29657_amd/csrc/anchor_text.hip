@@ -12,9 +12,8 @@
 // Every (row, head) softmax needs its normaliser before the head mean can be
 // formed, so the path has two passes over the keys:
 //
-// text_stats  task (sample, head, group of 1, 2 or 4 row blocks of 128; groups only
-//             when a sample has at most four row blocks[, key range]), XCD-aware; a
-//             batch with few such tasks splits their keys into ranges whose tables
+// text_stats  task (sample, head, group of one or two row blocks of 128[, key range]),
+//             XCD-aware; a batch with few such tasks splits their keys into ranges whose tables
 //             text_lse_merge combines.
 //             One key stream consumed by four waves of 32 rows per row block (the
 //             kernel also has a two-stream form of two 64-row waves each), so each
@@ -418,6 +417,16 @@ __device__ __forceinline__ void stats_task(
     }
 }
 
+// Whether the statistics tasks are dealt to the XCDs by units (below) instead of as eight
+// contiguous ranges.  A contiguous range holds whole samples, so with ragged samples the XCD
+// with the longest ones finished last while the others idled (mutual scoring of 16 samples of
+// 256-4096 keys, work ~ keys^2: statistics 697 -> 435 us, column sums 730 -> 470 us; ragged
+// grouped-query batch: statistics 493 -> 430 us).  Uniform batches keep the ranges; so do
+// fewer than eight units per XCD, whose remainder would leave XCDs idle.
+__host__ __device__ __forceinline__ bool stats_by_unit(const Prob& p, int ns) {
+    return (p.k_off || p.q_off) && (long long)p.B * p.Hkv * ns >= 8 * kXcds;
+}
+
 // One statistics task per workgroup.  Task = (sample, head, group of RBW row blocks),
 // groups fastest, XCD-aware: the groups of one (sample, head) read the same keys and
 // meet in one L2; the RBW row blocks of a group share one copy of every key block.
@@ -433,9 +442,31 @@ __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
     const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
     const int ngrp = (nrb + RBW - 1) / RBW;
     const int ns = COLSUM || p.lse_splits < 1 ? 1 : p.lse_splits;
-    const int task = xcd_remap((int)blockIdx.x, ngrp * p.H * p.B * ns);
-    const int split = task % ns, rest = task / ns;
-    const int tblk = rest % ngrp, h = (rest / ngrp) % p.H, b = rest / (ngrp * p.H);
+    int b, h, tblk, split;
+    if (stats_by_unit(p, ns)) {
+        // Unit = (sample, key head, key range): the row-block groups of the query heads that
+        // read the same keys.  Units are dealt to the XCDs in turn.
+        const int group = p.H / p.Hkv, per = group * ngrp;
+        const int j = (int)blockIdx.x / kXcds;
+        const int unit = j / per * kXcds + (int)blockIdx.x % kXcds, in = j % per;
+        if (unit >= p.B * p.Hkv * ns) return;
+        split = unit % ns;
+        tblk = in % ngrp;
+        h = (unit / ns) % p.Hkv * group + in / ngrp;
+        b = unit / (ns * p.Hkv);
+    } else {
+        const int task = xcd_remap((int)blockIdx.x, ngrp * p.H * p.B * ns);
+        const int rest = task / ns;
+        split = task % ns;
+        tblk = rest % ngrp;
+        h = (rest / ngrp) % p.H;
+        b = rest / (ngrp * p.H);
+    }
+    // Wave-uniform (the key copies take a scalar base address).
+    b = __builtin_amdgcn_readfirstlane(b);
+    h = __builtin_amdgcn_readfirstlane(h);
+    tblk = __builtin_amdgcn_readfirstlane(tblk);
+    split = __builtin_amdgcn_readfirstlane(split);
     stats_task<DS, HALF, COLSUM, RG, kStatsRing, RBW>(p, q, k, lse2, lse_in, lse_natural, part,
                                                       b, h, tblk, split, ns, smem_raw);
 }
@@ -875,7 +906,10 @@ static hipError_t stats_launch_rg(const Prob& p, const void* q, const void* k, f
     if (attr != hipSuccess) return attr;
     const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
     const int ns = COLSUM || p.lse_splits < 1 ? 1 : p.lse_splits;
-    dim3 grid((nrb + RBW - 1) / RBW * p.H * p.B * ns);
+    const int ngrp = (nrb + RBW - 1) / RBW;
+    const int units = p.B * p.Hkv * ns;
+    dim3 grid(stats_by_unit(p, ns) ? (units + kXcds - 1) / kXcds * kXcds * (p.H / p.Hkv) * ngrp
+                                   : ngrp * p.H * p.B * ns);
     const hipError_t e = launch(text_stats_kernel<DS, HALF, COLSUM, RG, RBW>, grid,
                                 dim3(kStatsThreads * RBW), smem, s, p,
                                 static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
@@ -894,21 +928,11 @@ template <int DS, bool HALF, bool COLSUM>
 static hipError_t stats_launch(const Prob& p, const void* q, const void* k, float* lse2,
                                const float* lse_in, int lse_natural, float* part,
                                const Finish& fin, hipStream_t s) {
-    // With two to four row blocks per sample, one workgroup takes two or four of them and
-    // copies each key block once for all: on the ragged Qwen3-VL batch (up to 4 row
-    // blocks) the pass fetches 1403 MB, its algorithmic bytes, instead of 1965 MB with
-    // one row block per workgroup (1722 MB with two), ~1 % faster.  Taller batches keep
-    // one row block per workgroup: the mutual-scoring Stage I of the same batch (up to 32
-    // row blocks) took 4.42 ms with four per workgroup, 3.84 ms with two, 3.83 ms with one.
-    if constexpr (!COLSUM) {
-        const int rbw = stats_row_blocks((p.max_rows + kTxtRows - 1) / kTxtRows);
-        if (rbw == 4)
-            return stats_launch_rg<DS, HALF, COLSUM, 4, 4>(p, q, k, lse2, lse_in, lse_natural, part,
-                                                           fin, s);
-        if (rbw == 2)
+    // The column sums keep one row block per workgroup (their partials are per row block).
+    if constexpr (!COLSUM)
+        if (stats_row_blocks((p.max_rows + kTxtRows - 1) / kTxtRows, !p.q_off) == 2)
             return stats_launch_rg<DS, HALF, COLSUM, 4, 2>(p, q, k, lse2, lse_in, lse_natural, part,
                                                            fin, s);
-    }
     return stats_launch_rg<DS, HALF, COLSUM, 4, 1>(p, q, k, lse2, lse_in, lse_natural, part, fin, s);
 }
 

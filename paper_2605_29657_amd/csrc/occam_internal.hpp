@@ -296,8 +296,16 @@ inline size_t text_score_smem(int H, int d16) {
 // the head slices faster than deeper rings at fewer workgroups per CU: the scattered
 // 256-byte slices stream better with fewer requests outstanding per CU.
 constexpr int kStatsRing = 2;
-// Row blocks per statistics workgroup for nrb 128-row blocks per sample (at most).
-inline int stats_row_blocks(int nrb) { return nrb == 2 ? 2 : (nrb == 3 || nrb == 4) ? 4 : 1; }
+// Row blocks per statistics workgroup for nrb 128-row blocks per sample (at most).  Two
+// share each key block's copy where both are nearly always there: an even uniform count, or
+// many of them (the last one alone, half idle, weighs little).  With few row blocks of
+// ragged samples the idle half costs more than the shared copies save: on the grouped-query
+// batch of 64 samples with 16-512 rows the pass takes 394 us with one, 443 us with two and
+// 430 us with four; video (256 rows) 317 us with one, 309 us with two; mutual scoring (up to
+// 33 row blocks) 419 us with one, 406 us with two.
+inline int stats_row_blocks(int nrb, bool uniform) {
+    return nrb >= 8 || (uniform && nrb % 2 == 0) ? 2 : 1;
+}
 // Key ranges of the statistics pass: a batch with fewer than kStatsMinWorkgroups
 // (sample, head, row-block group) tasks splits each task's keys into up to kStatsMaxSplits
 // ranges of at least kStatsMinSplitBlocks 32-key blocks; each range writes its own base-2
