@@ -228,10 +228,11 @@ occam_status occam_prune(const occam_problem *problem, const void *q, const void
 /* occam_prune without a workspace argument, for callers that cannot allocate
  * device memory (code under HIP graph capture, serving loops, harnesses that
  * forbid hipMalloc).  It runs exactly the kernels of occam_prune, with the
- * workspace taken from a static device array built into the library: 32 MiB per
+ * workspace taken from a static device array built into the library: 64 MiB per
  * GPU, held from the library's first use on that GPU until the process ends.
- * A problem whose occam_workspace_size exceeds 32 MiB returns
- * OCCAM_ERR_WORKSPACE (use occam_prune with a workspace of its own).  The
+ * A problem that needs more than 32 MiB, its row-block partials counted at 128
+ * rows per block, returns OCCAM_ERR_WORKSPACE (use occam_prune with a workspace
+ * of its own).  The
  * array's device address is looked up once per device, on the first call whose
  * stream belongs to that device (OCCAM_ERR_HIP if the lookup fails).  The call
  * allocates nothing.  Every call on one GPU shares that GPU's array, so calls

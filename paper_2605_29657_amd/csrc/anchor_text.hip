@@ -31,10 +31,11 @@
 //             writes per-(row block, head) column sums for mutual scoring (Eq.
 //             mutual_scoring, every key takes the mean over rows);
 //             text_colsum_reduce adds them in a fixed order.
-// text_score  one workgroup per (sample, block of 128 keys, row block).  Each
-//             wave owns 32 keys.  For every head the 128 x d query tile is copied
-//             global -> LDS (double-buffered) and the wave's key fragments are
-//             loaded into registers one head ahead, while p = 2^(x - lse2) of the
+// text_score  one workgroup per (sample, block of keys, row block): four waves and 64 rows,
+//             or eight waves and 128 rows (score_form).  Each wave owns 32 keys.  For
+//             every head the query tile (double-buffered) and the wave's keys are copied
+//             global -> LDS in whole lines one head ahead, and the key fragments then go
+//             to registers, while p = 2^(x - lse2) of the
 //             current head is accumulated over heads per (key, row); the workgroups
 //             of one XCD walk the heads from the same start.  Afterwards the row
 //             reduction of Eq. text_scoring is applied: max over rows for visual
@@ -51,6 +52,8 @@
 // When the caller supplies its own natural-log normaliser (row_lse), text_stats
 // is skipped and the second pass reads lse2 = row_lse * log2(e).
 #include "occam_internal.hpp"
+
+#include <algorithm>
 
 namespace occam {
 
@@ -479,14 +482,14 @@ __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
 // keeps a sample's tasks on one XCD.  Called by wave 0: each lane counts the tasks of a
 // run of consecutive samples, a scan finds the lane and sample holding the task, which
 // leaves (b, c, rb) in sh[0..2], or b = -1 past the last task.
-__device__ void ragged_score_task(const Prob& p, int id, int* sh) {
+__device__ void ragged_score_task(const Prob& p, int id, int kpw, int rb, int* sh) {
     const int lane = threadIdx.x;
     const int per = (p.B + kWave - 1) / kWave;
     const int i0 = min(lane * per, p.B), i1 = min(i0 + per, p.B);
     auto ntask = [&](int b) {
         const int T = rows_of(p, b), S = keys_of(p, b);
         if (T <= 0 || S <= 0) return 0;
-        return ((S + kTxtKeysPerWg - 1) / kTxtKeysPerWg) * ((T + kTxtRows - 1) / kTxtRows);
+        return ((S + kpw - 1) / kpw) * ((T + rb - 1) / rb);
     };
     int cnt = 0;
     for (int i = i0; i < i1; ++i) cnt += ntask(p.B - 1 - i);
@@ -506,7 +509,7 @@ __device__ void ragged_score_task(const Prob& p, int id, int* sh) {
     for (int i = i0; i < i1; ++i) {
         const int b = p.B - 1 - i, n = ntask(b);
         if (t < acc + n) {
-            const int nrb_b = (rows_of(p, b) + kTxtRows - 1) / kTxtRows;
+            const int nrb_b = (rows_of(p, b) + rb - 1) / rb;
             sh[0] = b;
             sh[1] = (t - acc) / nrb_b;
             sh[2] = (t - acc) % nrb_b;
@@ -516,45 +519,48 @@ __device__ void ragged_score_task(const Prob& p, int id, int* sh) {
     }
 }
 
-// One scoring task: keys [128 c, 128 c + 128) of sample b against its row block rb.
-// CC: the normalisers were written earlier in the same launch (by other workgroups), so
-// they are read with device-coherent loads.  cc_out: the scores / partials are read later
-// in the same launch by another workgroup, so they are written with device-coherent
-// stores.  rot_id picks the starting head (rot_id % 8 of 8 heads spread over H).
-template <int DS, bool HALF, bool FULL, bool CC>
+// One scoring task: keys [KPW c, KPW c + KPW) of sample b (KPW = 32 NW) against its row
+// block rb, by NW waves.  cc_out: the scores / partials are read later in the same launch
+// by another workgroup, so they are written with device-coherent stores.  rot_id picks the
+// starting head (rot_id % 8 of 8 heads spread over H).
+template <int DS, bool HALF, int NW, int NSB, bool FULL>
 __device__ __forceinline__ void score_task(
     const Prob& p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const float* __restrict__ lse, int lse_natural, float* __restrict__ scores,
     float* __restrict__ part, int b, int c, int rb, int rot_id, char* smem_raw, bool cc_out)
 {
-    // 4 waves: wave w owns the 32 keys [s_lo + 32 w, +32) and the 128 rows of the
-    // workgroup's row block (4 sub-blocks of 32 rows, one MFMA accumulator chain each).  Two workgroups share a CU, so one workgroup's MFMAs
-    // overlap the other's exponentials.
+    // Wave w owns the 32 keys [s_lo + 32 w, +32) and the RB rows of the workgroup's row
+    // block (NSB sub-blocks of 32 rows, one MFMA accumulator chain each).
     //
-    // The query tile of a head (128 rows x NCH 16-byte chunks) lives in LDS row-major
-    // with an XOR swizzle: chunk c of row t sits in unit t*NCH + (c ^ (t & SW)), SW =
-    // NCH - 1 when NCH is a power of two (else 0).  It is double-buffered: the next
-    // head's tile is copied global -> LDS directly (buffer loads) while the current
-    // head is computed, so the copy needs no registers and each head needs one
-    // barrier.  A copy writes 64 consecutive units, i.e. reads whole 256-byte row
-    // slices from memory; an MFMA fragment read (32 rows, one chunk each) touches 16
-    // distinct 16-byte bank groups per 16 lanes.
+    // Bound at full load by the matrix and vector work per logit (8 MFMAs and 48 vector
+    // operations per 32 x 32 x 128 block): a probe of that block with operands from LDS
+    // takes ~250 ns per SIMD on random data (206-219 ns without the LDS reads, 160 ns on
+    // constant data, i.e. the card's power limit shows); the video batch's 1025 blocks per
+    // SIMD take 440 ns each here, 500 before.  Keys loaded straight into the MFMA layout
+    // (32 lines touched per 1 KB load, ~58 cycles each) were the largest part of the load
+    // path before; whole-line copies take 16.
+    //
+    // Both operands of a head reach LDS by whole-line global -> LDS copies, row-major with
+    // an XOR swizzle: chunk c of row t sits in unit t*NCH + (c ^ (t & SW)), SW = NCH - 1
+    // when NCH is a power of two (else 0).  The query tile is shared by the waves and
+    // double-buffered (one barrier per head); a wave's 32 keys go to an area of its own,
+    // from which it takes its fragments into registers before the next head's copy starts,
+    // so one buffer is enough.
+    constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB;
     constexpr int NCH = 2 * DS;                                   // 16-byte chunks per row
-    constexpr int QTILE = kTxtRows * NCH;                         // 16-byte units per tile
-    constexpr int COPIES = QTILE / kWave / (kScoreThreads / kWave);  // per wave per tile
+    constexpr int QTILE = RB * NCH;                         // 16-byte units per tile
+    constexpr int KTILE = kTxtKeysPerWave * NCH;                  // units of one wave's keys
+    constexpr int QCOPIES = (QTILE / kWave + NW - 1) / NW;        // per wave per head
+    constexpr int KCOPIES = KTILE / kWave;                        // = DS
     constexpr int SW = (NCH & (NCH - 1)) == 0 ? NCH - 1 : 0;
-    u32x4* qt = reinterpret_cast<u32x4*>(smem_raw);                         // [2][QTILE]
-    float* l2t = reinterpret_cast<float*>(smem_raw + 2 * QTILE * 16);       // [H][128]
-    // With several row blocks (part != null) each task writes its row maximum (visual
-    // keys) or row sum (registers) to part[b][row block][key]; the scores are formed from
-    // them afterwards (text_rows_combine, or the last task of the sample).
-    const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
+    const int nrb = (p.max_rows + RB - 1) / RB;
     const int S = keys_of(p, b);
-    const int s_lo = c * kTxtKeysPerWg;
-    const int t0 = rb * kTxtRows;
+    const int s_lo = c * KPW;
+    const int t0 = rb * RB;
     if (s_lo >= S || t0 >= rows_of(p, b)) return;
     const int T = rows_of(p, b);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, lo = lane & 31;
     const int H = p.H, Hkv = p.Hkv, d = p.d, group = H / Hkv;
     const int qb = q_begin(p, b), kb0 = k_begin(p, b);
@@ -562,168 +568,158 @@ __device__ __forceinline__ void score_task(
     const int wkey0 = s_lo + wave * kTxtKeysPerWave;
     const bool wactive = wkey0 < S;
     const int R = p.R;
+    u32x4* qt = reinterpret_cast<u32x4*>(smem_raw);                         // [2][QTILE]
+    u32x4* kt = qt + 2 * QTILE + wave * KTILE;                              // this wave's keys
+    float* l2t = reinterpret_cast<float*>(smem_raw + (2 * QTILE + NW * KTILE) * 16);  // [H][RB]
     // Loop step hh works on head (hh + rot) mod H: a key row's head slices all sit at
     // the same offset within 8 KB rows, so workgroups moving through the heads in step
     // would load the same memory channels at the same time.  Eight starting heads,
     // spread over the H heads, balance the channels as well as H of them do; with one
     // start per XCD (rot_id % 8 is the XCD), the workgroups that share an L2 also share
-    // the query tile and key slices they are reading.  Steps past the last head repeat
-    // the last one (clamped prefetches).
+    // the query tile and key slices they are reading.
     const int nrot = H < 8 ? H : 8;
     const int rot = (int)((unsigned)rot_id % (unsigned)nrot) * (H / nrot);
     auto head_of = [&](int hh) {
-        const int hc = min(hh, H - 1) + rot;
+        const int hc = hh + rot;
         return hc >= H ? hc - H : hc;
     };
 
-    // Copy head hh's query tile (rows t0..t0+127) into buffer buf.  Copy j of this
-    // wave fills units U = (wave*COPIES + j)*64 + lane: row t = U / NCH, the chunk
+    // Copy head hh's query tile (rows t0 .. t0 + RB - 1) into buffer buf.  Copy j of this
+    // wave fills units U = (wave*QCOPIES + j)*64 + lane: row t = U / NCH, the chunk
     // stored there is (U % NCH) ^ (t & SW).  Rows past T_b are clamped (their lse2 is
     // +inf, so they weigh exactly 0); the pad chunk past d (HALF) reads chunk 0
     // instead, harmless because the matching key chunk is zero.  The per-lane byte
-    // offsets are fixed for a row block (set_rows); a head only moves the base.
-    uint32_t qoff[COPIES];
-    const char* qrows = nullptr;
-    auto set_rows = [&](int t0) {
+    // offsets are fixed; a head only moves the base.  The wave's keys likewise (keys past
+    // S_b are clamped and never written).
+    uint32_t qoff[QCOPIES], koff[KCOPIES];
 #pragma unroll
-        for (int j = 0; j < COPIES; ++j) {
-            const int U = (wave * COPIES + j) * kWave + lane;
-            const int t = min(U / NCH, T - t0 - 1), ch = (U % NCH) ^ ((U / NCH) & SW);
-            const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
-            qoff[j] = (uint32_t)(t * H * d + e) * 2u;
-        }
-        qrows = reinterpret_cast<const char*>(q + ((size_t)qb + t0) * H * d);
-    };
-    const uint32_t qt_lds = lds_addr(qt);
+    for (int j = 0; j < QCOPIES; ++j) {
+        const int U = (wave + NW * j) * kWave + lane;
+        const int t = min(U / NCH, T - t0 - 1), ch = (U % NCH) ^ ((U / NCH) & SW);
+        const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
+        qoff[j] = (uint32_t)(t * H * d + e) * 2u;
+    }
+#pragma unroll
+    for (int j = 0; j < KCOPIES; ++j) {
+        const int U = j * kWave + lane;
+        const int kc = U / NCH, ch = (U % NCH) ^ (kc & SW);
+        const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
+        koff[j] = (uint32_t)(min(wkey0 + kc, S - 1) * Hkv * d + e) * 2u;
+    }
+    const char* qrows = reinterpret_cast<const char*>(q + ((size_t)qb + t0) * H * d);
+    const char* ksample = reinterpret_cast<const char*>(k + (size_t)kb0 * Hkv * d);
+    const uint32_t qt_lds = lds_addr(qt), kt_lds = lds_addr(kt);
     auto copy_q = [&](int hh, int buf) {
         const char* base = qrows + (size_t)head_of(hh) * d * 2;
 #pragma unroll
-        for (int j = 0; j < COPIES; ++j)
-            dma16_async(base, qoff[j],
-                        qt_lds + (uint32_t)((buf * QTILE + (wave * COPIES + j) * kWave) * 16));
+        for (int j = 0; j < QCOPIES; ++j)
+            if ((QTILE / kWave) % NW == 0 || wave + NW * j < QTILE / kWave)
+                dma16_async(base, qoff[j],
+                            qt_lds + (uint32_t)((buf * QTILE + (wave + NW * j) * kWave) * 16));
     };
-    // Byte offset in a tile of fragment (row lo of a 32-row block, chunk hi) for k-step
-    // 0; k-step kk reads (qfrag ^ kk*32) with SW, (qfrag + kk*32) without.
-    const uint32_t qfrag = (uint32_t)(lo * NCH + (hi ^ (lo & SW))) * 16u;
-    // Key fragments: lane offset within the sample's key rows, fixed; the head picks the base.
-    const int kclamp = min(wkey0 + lo, S - 1);        // keys past S_b are never written
-    const uint32_t koff = (uint32_t)(kclamp * Hkv * d) * 2u;
-    const char* ksample = reinterpret_cast<const char*>(k + (size_t)kb0 * Hkv * d);
-    auto load_k = [&](int hh, u32x4 (&kf)[DS]) {
+    auto copy_k = [&](int hh) {
         const char* base = ksample + (size_t)(head_of(hh) / group) * d * 2;
 #pragma unroll
+        for (int j = 0; j < KCOPIES; ++j)
+            dma16_async(base, koff[j], kt_lds + (uint32_t)(j * kWave * 16));
+    };
+    // Does step hh need other keys than step hh - 1 (grouped-query heads share theirs)?
+    auto new_keys = [&](int hh) { return group == 1 || head_of(hh) / group != head_of(hh - 1) / group; };
+    // Byte offset of fragment (row lo of a 32-row block, chunk hi) for k-step 0; k-step kk
+    // reads (frag ^ kk*32) with SW, (frag + kk*32) without.
+    const uint32_t frag = (uint32_t)(lo * NCH + (hi ^ (lo & SW))) * 16u;
+    u32x4 kf[DS];
+    auto read_k = [&]() {
+#pragma unroll
         for (int kk = 0; kk < DS; ++kk) {
-            const bool pad = HALF && kk == DS - 1 && hi;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(
-                base + koff + (uint32_t)((kk * 16 + (pad ? 0 : hi * 8)) * 2));
+            const uint32_t fo = SW ? (frag ^ (uint32_t)(kk * 32)) : frag + kk * 32;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(kt) + fo);
             const u32x4 zero = {0u, 0u, 0u, 0u};
-            kf[kk] = pad ? zero : v;
+            kf[kk] = (HALF && kk == DS - 1 && hi) ? zero : v;
         }
     };
 
-    float abar[4][16];
-    {
-        const int nsb = min(4, (T - t0 + 31) >> 5);
-        for (int i = tid; i < H * kTxtRows; i += kScoreThreads) {
-            const int hh = i / kTxtRows, t = t0 + (i % kTxtRows);
-            float v = INFINITY;
-            if (t < T) {
-                const float* src = lse + (size_t)(qb + t) * H + hh;
-                v = CC ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
-                if (lse_natural) v *= kLog2e;
-            }
-            l2t[i] = v;
+    copy_k(0);
+    copy_q(0, 0);
+    const int nsb = min(NSB, (T - t0 + 31) >> 5);
+    for (int i = tid; i < H * RB; i += kWave * NW) {
+        const int hh = i / RB, t = t0 + (i % RB);
+        float v = INFINITY;
+        if (t < T) {
+            v = lse[(size_t)(qb + t) * H + hh];
+            if (lse_natural) v *= kLog2e;
         }
-        u32x4 k0[DS], k1[DS];
-        set_rows(t0);
-        load_k(0, k0);
-        copy_q(0, 0);
-        wait_vmem();
+        l2t[i] = v;
+    }
+    float abar[NSB][16];
 #pragma unroll
-        for (int kk = 0; kk < DS; ++kk) settle(k0[kk]);
-        __syncthreads();
+    for (int sb = 0; sb < NSB; ++sb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) abar[sb][r] = 0.f;
+    wait_vmem();
+    read_k();
+#pragma unroll
+    for (int kk = 0; kk < DS; ++kk) settle(kf[kk]);
+    __syncthreads();
 
+    for (int h = 0; h < H; ++h) {
+        // Start the copies of head h+1, then the MFMA logits of the wave's 32 keys x RB
+        // rows, p = 2^(x - lse2) and the head sum; then wait for the copies, take the next
+        // key fragments and synchronise.
+        const int buf = h & 1;
+        const bool more = h + 1 < H;
+        const bool nk = more && new_keys(h + 1);
+        if (more) copy_q(h + 1, buf ^ 1);
+        if (nk) copy_k(h + 1);
+        if (wactive) {
+            const char* qtile = reinterpret_cast<const char*>(qt) + buf * QTILE * 16;
+            const float* l2h = l2t + head_of(h) * RB + lo;
+            auto chain = [&](int sp) {
+                f32x16 acc = {};
 #pragma unroll
-        for (int sb = 0; sb < 4; ++sb)
+                for (int kk = 0; kk < DS; ++kk) {
+                    const uint32_t fo = SW ? (frag ^ (uint32_t)(kk * 32)) : frag + kk * 32;
+                    const u32x4 qv = *reinterpret_cast<const u32x4*>(qtile + sp * 32 * NCH * 16 + fo);
+                    acc = mfma32(as_bf16x8(kf[kk]), as_bf16x8(qv), acc);
+                }
+                return acc;
+            };
+            auto soft = [&](int sp, const f32x16& acc) {
+                const float l2 = l2h[sp * 32];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) abar[sb][r] = 0.f;
-
-        // One head: start the copies of head h+1 (query tile to the other buffer, key
-        // fragments to registers), MFMA logits of the wave's 32 keys x 128 rows (two
-        // accumulator chains at a time), p = 2^(x - lse2), head sum; then wait for the
-        // copies and synchronise.
-        auto head = [&](int h, const u32x4 (&kf)[DS], u32x4 (&kn)[DS]) {
-            const int buf = h & 1;
-            // Nothing of this wave is in flight here except compiler reloads; waiting for
-            // them now keeps the compiler from waiting inside the head, where that wait
-            // would also cover the copies issued next.
-            wait_vmem();
-            copy_q(h + 1, buf ^ 1);
-            load_k(h + 1, kn);
-            if (wactive) {
-                const char* qtile = reinterpret_cast<const char*>(qt) + buf * QTILE * 16;
-                // MFMA logits of the wave's 32 keys x one 32-row sub-block (one accumulator
-                // chain), and p = 2^(x - lse2) of a finished chain added to the head sum.
-                auto chain = [&](int sp) {
-                    f32x16 acc = {};
+                for (int r = 0; r < 16; ++r)
+                    abar[sp][r] += __builtin_amdgcn_exp2f(fmaf(acc[r], c2, -l2));
+            };
+            // The chain of sub-block sp+1 is issued next to the exponentials of
+            // sub-block sp (scheduling barriers keep each pair together), so the wave
+            // keeps the matrix core and the vector unit busy at once; left to itself
+            // the compiler issues all 32 MFMAs first.
+            if (FULL || nsb == NSB) {
+                f32x16 a[2];
+                a[0] = chain(0);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int kk = 0; kk < DS; ++kk) {
-                        const uint32_t fo = SW ? (qfrag ^ (uint32_t)(kk * 32)) : qfrag + kk * 32;
-                        const u32x4 qv = *reinterpret_cast<const u32x4*>(qtile + sp * 32 * NCH * 16 + fo);
-                        acc = mfma32(as_bf16x8(kf[kk]), as_bf16x8(qv), acc);
-                    }
-                    return acc;
-                };
-                auto soft = [&](int sp, const f32x16& acc) {
-                    const float l2 = l2t[head_of(h) * kTxtRows + sp * 32 + lo];
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        abar[sp][r] += __builtin_amdgcn_exp2f(fmaf(acc[r], c2, -l2));
-                };
-                // The chain of sub-block sp+1 is issued next to the exponentials of
-                // sub-block sp (scheduling barriers keep each pair together), so the wave
-                // keeps the matrix core and the vector unit busy at once; left to itself
-                // the compiler issues all 32 MFMAs first.
-                auto pipelined = [&]() {
-                    f32x16 a0 = chain(0);
+                for (int sp = 1; sp < NSB; ++sp) {
+                    a[sp & 1] = chain(sp);
+                    soft(sp - 1, a[(sp - 1) & 1]);
                     __builtin_amdgcn_sched_barrier(0);
-                    f32x16 a1 = chain(1);
-                    soft(0, a0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    a0 = chain(2);
-                    soft(1, a1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    a1 = chain(3);
-                    soft(2, a0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    soft(3, a1);
-                };
-                if constexpr (FULL) {
-                    // Every row block full (FULL: uniform T, a multiple of 128).  With one
-                    // workgroup per CU (few keys per sample) the pipelined order is 13 %
-                    // faster.  A separate instantiation: the two forms in one kernel need
-                    // more registers, and the uniform batches run slower with them.
-                    pipelined();
-                } else if (nsb == 4) {
-                    // A full row block of a ragged or partial batch takes the same order
-                    // (Qwen3-VL batch: ~1 % faster step).
-                    pipelined();
-                } else {
+                }
+                soft(NSB - 1, a[(NSB - 1) & 1]);
+            } else {
 #pragma unroll
-                    for (int sp = 0; sp < 4; ++sp) {
-                        if (sp >= nsb) break;
-                        soft(sp, chain(sp));
-                    }
+                for (int sp = 0; sp < NSB; ++sp) {
+                    if (sp >= nsb) break;
+                    soft(sp, chain(sp));
                 }
             }
-            wait_vmem();
-            __syncthreads();
-        };
-        for (int h = 0; h < H; h += 2) {
-            head(h, k0, k1);
-            if (h + 1 >= H) break;
-            head(h + 1, k1, k0);
         }
+        wait_vmem();
+        if (nk) {
+            read_k();
+#pragma unroll
+            for (int kk = 0; kk < DS; ++kk) settle(kf[kk]);
+        }
+        __syncthreads();
     }
 
     // Row reduction of Eq. text_scoring (visual keys: max over rows, registers: mean):
@@ -733,8 +729,13 @@ __device__ __forceinline__ void score_task(
     float mx[16], sm[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        mx[r] = fmaxf(fmaxf(abar[0][r], abar[1][r]), fmaxf(abar[2][r], abar[3][r]));
-        sm[r] = (abar[0][r] + abar[1][r]) + (abar[2][r] + abar[3][r]);
+        mx[r] = abar[0][r];
+        sm[r] = abar[0][r];
+#pragma unroll
+        for (int sb = 1; sb < NSB; ++sb) {
+            mx[r] = fmaxf(mx[r], abar[sb][r]);
+            sm[r] += abar[sb][r];
+        }
 #pragma unroll
         for (int off = 16; off >= 1; off >>= 1) {
             mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], off));
@@ -765,22 +766,23 @@ __device__ __forceinline__ void score_task(
 // With fin.done, the last workgroup of each sample forms its scores from the row blocks'
 // partials (text_rows_combine's arithmetic) and, with fin.select, applies the threshold
 // and the compaction (select_kernel's arithmetic).
-template <int DS, bool HALF, bool FULL>
-__global__ __launch_bounds__(kScoreThreads, 2) void text_score_kernel(
+template <int DS, bool HALF, int NW, int NSB, bool FULL>
+__global__ __launch_bounds__(NW * kWave, 2) void text_score_kernel(
     Prob p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const float* __restrict__ lse, int lse_natural, float* __restrict__ scores,
     float* __restrict__ part, Finish fin)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-    const int nchunk = (p.R + p.max_cands + kTxtKeysPerWg - 1) / kTxtKeysPerWg;
-    const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
+    constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB, NT = NW * kWave;
+    const int nchunk = (p.R + p.max_cands + KPW - 1) / KPW;
+    const int nrb = (p.max_rows + RB - 1) / RB;
     int b, c, rb;
     if (p.k_off || p.q_off) {
         // The decoded task passes through the start of query buffer 1 (after the first
         // 128 x d tile), which is first written (head 1's copy) after the barrier that
         // ends the task's prologue.
-        int* sh = reinterpret_cast<int*>(smem_raw + (size_t)kTxtRows * 2 * DS * 16);
-        if (threadIdx.x < kWave) ragged_score_task(p, (int)blockIdx.x, sh);
+        int* sh = reinterpret_cast<int*>(smem_raw + (size_t)RB * 2 * DS * 16);
+        if (threadIdx.x < kWave) ragged_score_task(p, (int)blockIdx.x, KPW, RB, sh);
         __syncthreads();
         b = sh[0];
         if (b < 0) return;
@@ -799,12 +801,12 @@ __global__ __launch_bounds__(kScoreThreads, 2) void text_score_kernel(
     // XCD's L2.  A start per key chunk instead fetched 1062 MB per launch at the
     // LLaVA-NeXT shape and 3586 MB on the ragged Qwen3-VL batch; per XCD, 807 and 2654 MB,
     // ~1 % faster.
-    score_task<DS, HALF, FULL, false>(p, q, k, lse, lse_natural, scores, part, b, c, rb,
+    score_task<DS, HALF, NW, NSB, FULL>(p, q, k, lse, lse_natural, scores, part, b, c, rb,
                                       (int)blockIdx.x, smem_raw, fin.done != nullptr);
     if (!fin.done) return;
     const int S = keys_of(p, b), T = rows_of(p, b);
-    const int nrb_b = (T + kTxtRows - 1) / kTxtRows;
-    const unsigned ntask = (unsigned)(((S + kTxtKeysPerWg - 1) / kTxtKeysPerWg) * nrb_b);
+    const int nrb_b = (T + RB - 1) / RB;
+    const unsigned ntask = (unsigned)(((S + KPW - 1) / KPW) * nrb_b);
     if (!last_of_sample(fin.done, b, ntask, reinterpret_cast<int*>(smem_raw + 64))) return;
     if (part) {
         // Row maxima (visual keys) / row sums (registers) over the row blocks in order,
@@ -818,7 +820,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void text_score_kernel(
         float* out = scores + k_begin(p, b);
         float* sl = fin.select ? select_scores_lds(smem_raw + 128) : nullptr;
         const float inv_reg = 1.f / ((float)p.H * (float)T), inv_vis = 1.f / (float)p.H;
-        for (int s0 = threadIdx.x; s0 < S; s0 += U * kScoreThreads) {
+        for (int s0 = threadIdx.x; s0 < S; s0 += U * NT) {
             float v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = 0.f;
@@ -826,16 +828,16 @@ __global__ __launch_bounds__(kScoreThreads, 2) void text_score_kernel(
                 float x[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int s = s0 + u * kScoreThreads;
+                    const int s = s0 + u * NT;
                     x[u] = s < S ? ld<true>(pb + (size_t)r * smax + s) : 0.f;
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    v[u] = s0 + u * kScoreThreads < p.R ? v[u] + x[u] : fmaxf(v[u], x[u]);
+                    v[u] = s0 + u * NT < p.R ? v[u] + x[u] : fmaxf(v[u], x[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int s = s0 + u * kScoreThreads;
+                const int s = s0 + u * NT;
                 if (s < S) {
                     const float w = v[u] * (s < p.R ? inv_reg : inv_vis);
                     st_cc(out + s, w);
@@ -845,22 +847,23 @@ __global__ __launch_bounds__(kScoreThreads, 2) void text_score_kernel(
         }
         if (fin.select) {
             __syncthreads();
-            select_sample(p, scores, b, fin, smem_raw + 128, true);
+            select_sample<NT>(p, scores, b, fin, smem_raw + 128, true);
         }
         return;
     }
-    if (fin.select) select_sample(p, scores, b, fin, smem_raw + 128, false);
+    if (fin.select) select_sample<NT>(p, scores, b, fin, smem_raw + 128, false);
 }
 
 // Scores from the row blocks' partials: the maximum over row blocks (visual keys) or
 // the sum in row-block order (registers), then the head mean (and row mean).
-__global__ __launch_bounds__(256) void text_rows_combine_kernel(Prob p, const float* __restrict__ part,
+__global__ __launch_bounds__(256) void text_rows_combine_kernel(Prob p, int rb_rows,
+                                                                const float* __restrict__ part,
                                                                 float* __restrict__ scores)
 {
     const int b = blockIdx.y, s = blockIdx.x * 256 + threadIdx.x;
     const int S = keys_of(p, b), T = rows_of(p, b);
     if (s >= S) return;
-    const int nrb_max = (p.max_rows + kTxtRows - 1) / kTxtRows, nrb = (T + kTxtRows - 1) / kTxtRows;
+    const int nrb_max = (p.max_rows + rb_rows - 1) / rb_rows, nrb = (T + rb_rows - 1) / rb_rows;
     const size_t smax = (size_t)(p.R + p.max_cands);
     const float* pb = part + (size_t)b * nrb_max * smax + s;
     float v = 0.f;
@@ -975,39 +978,37 @@ __global__ __launch_bounds__(256) void text_colsum_reduce_kernel(Prob p, const f
     scores[k_begin(p, b) + s] = T > 0 ? acc * (1.f / ((float)p.H * (float)T)) : 0.f;
 }
 
-template <int DS, bool HALF, bool FULL>
+template <int DS, bool HALF, int NW, int NSB, bool FULL>
 static hipError_t score_launch(const Prob& p, const void* q, const void* k, const float* lse,
                                int lse_natural, float* scores, float* part, const Finish& fin,
                                hipStream_t s) {
-    const size_t smem = text_score_smem(p.H, DS * 16);
-    // The tile needs more than the default 64 KB of dynamic LDS: raise the limit (once per
+    constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB;
+    size_t smem = score_smem(ScoreForm{NW, RB}, p.H, DS * 16);
+    if (fin.select) smem = std::max(smem, 128 + select_lds_bytes(p.R, p.max_cands));
+    // The tiles need more than the default 64 KB of dynamic LDS: raise the limit (once per
     // device).
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t attr = allow_lds(
-        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, FULL>), (int)kScoreSmemMax,
+        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, NW, NSB, FULL>), (int)kScoreSmemMax,
         lds_set);
     if (attr != hipSuccess) return attr;
-    const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
-    dim3 grid((p.R + p.max_cands + kTxtKeysPerWg - 1) / kTxtKeysPerWg * nrb * p.B);
-    return launch(text_score_kernel<DS, HALF, FULL>, grid, dim3(kScoreThreads), smem, s, p,
-                  static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), lse,
-                  lse_natural, scores, nrb > 1 ? part : nullptr, fin);
+    const int nrb = (p.max_rows + RB - 1) / RB;
+    dim3 grid((p.R + p.max_cands + KPW - 1) / KPW * nrb * p.B);
+    const hipError_t e = launch(text_score_kernel<DS, HALF, NW, NSB, FULL>, grid, dim3(NW * kWave), smem, s,
+                                p, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                                lse, lse_natural, scores, nrb > 1 ? part : nullptr, fin);
+    if (e != hipSuccess || nrb == 1 || fin.done) return e;
+    dim3 cgrid((p.R + p.max_cands + 255) / 256, p.B);
+    return launch(text_rows_combine_kernel, cgrid, dim3(256), 0, s, p, RB, part, scores);
 }
 
 template <int DS, bool HALF>
 static hipError_t score_ds(const Prob& p, const void* q, const void* k, const float* lse,
                            int lse_natural, float* scores, float* part, const Finish& fin,
                            hipStream_t s) {
-    // Uniform rows that fill whole 128-row blocks take the pipelined form.
-    const bool full = !p.q_off && p.rows == p.max_rows && p.rows % kTxtRows == 0;
-    const hipError_t e =
-        full ? score_launch<DS, HALF, true>(p, q, k, lse, lse_natural, scores, part, fin, s)
-             : score_launch<DS, HALF, false>(p, q, k, lse, lse_natural, scores, part, fin, s);
-    if (e != hipSuccess) return e;
-    const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
-    if (nrb == 1 || fin.done) return hipSuccess;
-    dim3 cgrid((p.R + p.max_cands + 255) / 256, p.B);
-    return launch(text_rows_combine_kernel, cgrid, dim3(256), 0, s, p, part, scores);
+    if (score_form(p).waves == 8)
+        return score_launch<DS, HALF, 8, 4, true>(p, q, k, lse, lse_natural, scores, part, fin, s);
+    return score_launch<DS, HALF, 4, 2, false>(p, q, k, lse, lse_natural, scores, part, fin, s);
 }
 
 // d = 16*DS (HALF = false) or 16*DS - 8 (HALF = true), d <= 128.

@@ -26,6 +26,7 @@ struct Plan {
     int nchunks;       // key chunks per sample of the one-row path
     size_t off_logits, off_stats, off_lse2, off_part, off_done, off_clist, off_ccnt, off_scores,
         off_tau, off_slot, off_match, total;
+    size_t finer;      // bytes of off_part beyond what 128-row blocks would take
 };
 
 bool aligned(const void* ptr, size_t a) { return (reinterpret_cast<uintptr_t>(ptr) % a) == 0; }
@@ -73,7 +74,11 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         if ((long long)max_rows * H * d * 2 >= (1LL << 32) ||
             (R + (long long)max_cands) * x.num_kv_heads * d * 2 >= (1LL << 32))
             return OCCAM_ERR_UNSUPPORTED;
-        if (text_score_smem(H, ((d + 15) / 16) * 16) > kScoreSmemMax) return OCCAM_ERR_UNSUPPORTED;
+        // The most heads a row block's normaliser table has room for beside its query tiles.
+        const int d16 = (d + 15) / 16 * 16;
+        if (2 * (size_t)kTxtRows * d16 * 2 + (size_t)H * kTxtRows * 4 > kScoreSmemMax)
+            return OCCAM_ERR_UNSUPPORTED;
+        const ScoreForm form = score_form(P.p);
         const size_t nrb = (max_rows + kTxtRows - 1) / kTxtRows;
         // The statistics pass of a small batch splits every task's keys into ranges, each
         // with its own normaliser table (the scoring pass merges them); not for mutual scoring.
@@ -87,9 +92,13 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         if (P.p.mean_rows) {
             // Column sums of mutual scoring, per (sample, 128-row block, head, key).
             off = align_up(off + (size_t)B * nrb * H * (R + (size_t)max_cands) * sizeof(float));
-        } else if (nrb > 1) {
-            // Row maxima / sums of the max form, per (sample, 128-row block, key).
-            off = align_up(off + (size_t)B * nrb * (R + (size_t)max_cands) * sizeof(float));
+        } else if (max_rows > form.rows) {
+            // Row maxima / sums of the max form, per (sample, row block, key).
+            const size_t blocks = (max_rows + form.rows - 1) / form.rows;
+            const size_t block = (size_t)B * (R + (size_t)max_cands) * sizeof(float);
+            const size_t coarse = nrb > 1 ? align_up(off + nrb * block) : off;
+            off = align_up(off + blocks * block);
+            P.finer = off - coarse;
         }
     } else {
         P.kpw = cls_keys_per_wg(H, x.num_kv_heads, d, bf16 ? 2 : 4, B, R + (long long)max_cands);
@@ -180,12 +189,15 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
     if (selected) *selected = 0;
     if (P.text) {
         // Text rows: the sample's last scoring workgroup combines the row blocks and, when
-        // the copy of the sample's scores fits in the kernel's LDS, selects.  The counters
+        // the copy of the sample's scores fits in the kernel's LDS (or in half a CU's, which
+        // keeps two workgroups there), selects.  The counters
         // are cleared by the statistics kernel, so not with a caller normaliser.
         const bool counters = !row_lse && !P.p.mean_rows;
-        const bool combine = P.p.max_rows > kTxtRows;
+        const ScoreForm form = score_form(P.p);
+        const bool combine = P.p.max_rows > form.rows;
         const size_t need = 128 + select_lds_bytes(P.p.R, P.p.max_cands);
-        const bool do_select = sel && need <= text_score_smem(P.p.H, ((P.p.d + 15) / 16) * 16);
+        const size_t room = score_smem(form, P.p.H, (P.p.d + 15) / 16 * 16);
+        const bool do_select = sel && need <= (room > kScoreSmemMax / 2 ? room : kScoreSmemMax / 2);
         if (counters && (do_select || combine)) {
             if (sel) fin = *sel;
             fin.done = ws_at<unsigned>(ws, P.off_done);
@@ -297,7 +309,9 @@ occam_status run_prune(const Plan& P, const void* q, const void* k, const float*
 // (held until the process ends).  In host code `scratch` names a host-side stand-in, not
 // device memory: only the address that hipGetSymbolAddress returns for the device,
 // looked up once per device and kept in scratch_ptr, is ever handed to a kernel.
-constexpr size_t kScratchBytes = size_t(32) << 20;
+// kScratchLimit bounds what a problem may need beside its finer row blocks' partials (which
+// never exceed the rest).
+constexpr size_t kScratchLimit = size_t(32) << 20, kScratchBytes = 2 * kScratchLimit;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -455,7 +469,7 @@ occam_status occam_prune_noalloc(const occam_problem* problem, const void* q, co
     occam_status st = prune_args(problem, q, k, row_lse, lambda, reduce, index_map, n, tensors,
                                  scores, tau, kept_idx, kept_count, kept_offsets, &P, &rows);
     if (st != OCCAM_OK) return st;
-    if (P.total > kScratchBytes) return OCCAM_ERR_WORKSPACE;
+    if (P.total - P.finer > kScratchLimit || P.total > kScratchBytes) return OCCAM_ERR_WORKSPACE;
     void* ws = scratch_for(stream);
     if (!ws) return OCCAM_ERR_HIP;
     return run_prune(P, q, k, row_lse, lambda, reduce, index_map, rows, scores, tau, kept_idx,

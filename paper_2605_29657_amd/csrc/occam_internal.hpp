@@ -259,14 +259,11 @@ struct RowTensors {
 // Anchor (T = 1) path: VALU dot products, KPW keys per workgroup.
 constexpr int kClsThreads = 256;
 constexpr int kClsPartials = 8192;   // LDS floats of per-chunk partial dot products
-// Text (T > 1) path: MFMA 32x32x16 bf16; 4 waves; a t-block of 128 anchor rows
-// (4 sub-blocks of 32) and 32 keys per wave.
-constexpr int kTxtThreads = 256;
+// Text (T > 1) path: MFMA 32x32x16 bf16; statistics on blocks of 128 anchor rows (4 waves
+// of 32), scoring on 32 keys per wave (score_form).
 constexpr int kStatsThreads = 256;
-constexpr int kScoreThreads = 256;
 constexpr int kTxtRows = 128;
 constexpr int kTxtKeysPerWave = 32;
-constexpr int kTxtKeysPerWg = 128;   // score kernel: 4 key blocks of 32
 constexpr int kSelThreads = 256;    // threshold, top-K, budget matching; reference-sum order
 constexpr int kSelectThreads = 512; // the select kernel (its reference sum uses kSelThreads)
 constexpr int kGatherThreads = 256;
@@ -283,11 +280,34 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
     return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
 }
 
-// Dynamic LDS of the text-row scoring kernel: two query tiles (128 rows x d bf16)
-// and the [H][128] float normaliser tile; at most kScoreSmemMax.
+// Forms of the text-row scoring kernel: waves per workgroup (32 keys each) and anchor rows
+// per workgroup.  LDS: two query tiles (rows x d bf16), the waves' keys and the [H][rows]
+// float normaliser table; at most kScoreSmemMax.
 constexpr size_t kScoreSmemMax = 160 * 1024;
-inline size_t text_score_smem(int H, int d16) {
-    return 2 * (size_t)kTxtRows * d16 * 2 + (size_t)H * kTxtRows * 4;
+struct ScoreForm {
+    int waves, rows;
+};
+inline size_t score_smem(const ScoreForm& f, int H, int d16) {
+    return (2 * (size_t)f.rows + (size_t)f.waves * kTxtKeysPerWave) * d16 * 2 +
+           (size_t)H * f.rows * 4;
+}
+// The wide form shares a query tile among twice as many keys and holds twice the rows, so it
+// reads both operands fewer times; it wants whole row blocks and a workgroup for every CU
+// (its LDS leaves room for one).  Video batch (8 x 16384 keys x 256 rows, 1040 wide
+// workgroups): 465 us against 549 us for the narrow form and 522 us for the one before
+// (four waves, 128 rows, keys straight into registers); LLaVA-NeXT (384): 219, 221 and 220.
+// Elsewhere the narrow form's finer tasks win: ragged grouped-query batch (64 samples of
+// 256-4096 keys and 16-512 rows) 427 us against 449 and 470; 32 chained samples of 64-1100
+// keys x 128 rows 70 against 93 and 80; one image (2880 keys x 128 rows) 47, 79 and 63.
+inline ScoreForm score_form(const Prob& p) {
+    const ScoreForm wide{8, 128}, narrow{4, 64};
+    const long long kpw = (long long)wide.waves * kTxtKeysPerWave;
+    const long long tasks = (long long)p.B * ((p.R + (long long)p.max_cands + kpw - 1) / kpw) *
+                            (p.max_rows / wide.rows);
+    return !p.q_off && p.rows % wide.rows == 0 && tasks >= 256 &&
+                   score_smem(wide, p.H, (p.d + 15) / 16 * 16) <= kScoreSmemMax
+               ? wide
+               : narrow;
 }
 
 // Dynamic LDS of the text-row statistics kernel: a ring of kStatsRing key blocks
@@ -414,7 +434,7 @@ __device__ __forceinline__ bool last_of_sample(unsigned* done, int b, unsigned n
 }
 
 // LDS the per-sample epilogue needs: its scratch words and a copy of the sample's scores.
-constexpr size_t kSelectScratch = 64;
+constexpr size_t kSelectScratch = 128;
 inline size_t select_lds_bytes(int R, int max_cands) {
     return kSelectScratch + 4 * ((size_t)R + (size_t)max_cands);
 }
@@ -425,30 +445,32 @@ __device__ __forceinline__ float* select_scores_lds(char* lds) {
 }
 
 // Threshold (tau_b = lambda * reference, the fused threshold of select_kernel) and
-// compaction of sample b by one workgroup of kSelThreads threads.  The sample's scores,
-// written by other workgroups of the launch, are first copied into LDS with
-// device-coherent loads (eight in flight per thread), unless the caller has already put
-// them there (in_lds, followed by a barrier); the reference and the compaction then read
-// the copy, with select_kernel's arithmetic.  lds: select_lds_bytes(R, N_b).
+// compaction of sample b by one workgroup of NT threads (kSelThreads or more).  The
+// sample's scores, written by other workgroups of the launch, are first copied into LDS
+// with device-coherent loads (eight in flight per thread), unless the caller has already
+// put them there (in_lds, followed by a barrier); the reference and the compaction then
+// read the copy, with select_kernel's arithmetic.  lds: select_lds_bytes(R, N_b).
+template <int NT>
 __device__ __forceinline__ void select_sample(const Prob& p, const float* scores, int b,
                                               const Finish& f, char* lds, bool in_lds) {
     float* red = reinterpret_cast<float*>(lds);              // kSelThreads / 64 floats
-    int* wsum = reinterpret_cast<int*>(lds + 16);            // kSelThreads / 64 ints
-    float* tau_s = reinterpret_cast<float*>(lds + 32);
+    float* tau_s = reinterpret_cast<float*>(lds + 16);
+    int* wsum = reinterpret_cast<int*>(lds + 32);            // NT / 64 ints
+    static_assert(NT >= kSelThreads && NT / kWave <= 16, "scratch layout");
     float* sl = select_scores_lds(lds);
     const int S = keys_of(p, b);
     const float* src = scores + k_begin(p, b);
     constexpr int U = 8;
-    for (int i0 = threadIdx.x; i0 < S && !in_lds; i0 += U * kSelThreads) {
+    for (int i0 = threadIdx.x; i0 < S && !in_lds; i0 += U * NT) {
         float v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * kSelThreads;
+            const int i = i0 + u * NT;
             v[u] = i < S ? ld<true>(src + i) : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * kSelThreads;
+            const int i = i0 + u * NT;
             if (i < S) sl[i] = v[u];
         }
     }
@@ -459,7 +481,7 @@ __device__ __forceinline__ void select_sample(const Prob& p, const float* scores
         *tau_s = t;
     }
     __syncthreads();
-    compact_of<kSelThreads>(sl + p.R, S - p.R, *tau_s, f.slot + cand_begin(p, b), f.count + b,
+    compact_of<NT>(sl + p.R, S - p.R, *tau_s, f.slot + cand_begin(p, b), f.count + b,
                             wsum);
 }
 
