@@ -89,17 +89,19 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         P.off_lse2 = off;
         off = align_up(off + (size_t)P.p.lse_splits * rows_cap * H * sizeof(float));
         P.off_part = off;
+        const size_t block = (size_t)B * (R + (size_t)max_cands) * sizeof(float);
         if (P.p.mean_rows) {
             // Column sums of mutual scoring, per (sample, 128-row block, head, key).
-            off = align_up(off + (size_t)B * nrb * H * (R + (size_t)max_cands) * sizeof(float));
-        } else if (max_rows > form.rows) {
-            // Row maxima / sums of the max form, per (sample, row block, key).
-            const size_t blocks = (max_rows + form.rows - 1) / form.rows;
-            const size_t block = (size_t)B * (R + (size_t)max_cands) * sizeof(float);
-            const size_t coarse = nrb > 1 ? align_up(off + nrb * block) : off;
-            off = align_up(off + blocks * block);
-            P.finer = off - coarse;
+            off = align_up(off + nrb * H * block);
+        } else if (nrb > 1) {
+            // Row maxima / sums of the max form, per (sample, 128-row block, key).
+            off = align_up(off + nrb * block);
         }
+        // Right behind them, what the max form's 64-row blocks take beyond that (either
+        // reduction reserves it, so that the two differ by the column sums alone).
+        const size_t blocks = (max_rows + form.rows - 1) / form.rows;
+        if (blocks > 1) P.finer = align_up((blocks - (nrb > 1 ? nrb : 0)) * block);
+        off += P.finer;
     } else {
         P.kpw = cls_keys_per_wg(H, x.num_kv_heads, d, bf16 ? 2 : 4, B, R + (long long)max_cands);
         const int NC = d / (bf16 ? 8 : 4);
