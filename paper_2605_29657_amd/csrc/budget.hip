@@ -13,19 +13,29 @@
 // Ratios are mapped to unsigned keys that order like the floats, and the c-th largest
 // key is found by a radix select, 8 bits per pass from the top:
 //   match_init   one workgroup: clears the selection state, counts M, sets c.
-//   match_hist   grid (B, candidate chunks of 1024): LDS histogram of the pass's digit
-//                over the keys that match the prefix chosen so far, added into one
+//   match_hist   grid (B, candidate chunks of 4096): the first pass forms the keys and
+//                leaves them in the workspace; every pass takes an LDS histogram of its
+//                digit over the keys that match the prefix chosen so far, added into one
 //                global histogram; the last workgroup to finish picks the digit and
 //                the rank left inside it.
 //   match_count  same grid: #{key >= v1}, #{key > v1}, the nearest keys above and
 //                below v1; the last workgroup chooses the level and writes lambda.
-// Every workgroup recomputes its sample's reference (s_b(r), or the mean visual score
-// of the ablation) with the same reduction as the threshold kernels.
+// The first pass's workgroups form their sample's reference (s_b(r), or the mean visual
+// score of the ablation) with the same reduction as the threshold kernels.
+//
+// Every pass moves under a megabyte at calibration sizes, so it is bound by latency: the
+// loads, the atomics (the top digit of a batch's ratios takes two or three values, so
+// they meet on a few addresses: 1024-thread workgroups add once per bin for 4096 keys, and
+// an LDS bin has eight copies on different banks) and the hand-over to the last workgroup
+// (relaxed device-scope atomics behind a wait, no cache-wide fence).  64 samples of 2880
+// candidates: 90.3 us in six launches with 256-thread workgroups, fences and the keys
+// formed in every pass, 29.0 us now.
 #include "occam_internal.hpp"
 
 namespace occam {
 
-constexpr int kMatchThreads = kSelThreads;      // same reference bits as occam_threshold
+constexpr int kMatchThreads = 1024;
+constexpr int kMatchCopies = 8, kMatchStride = 256 + 8;   // LDS histogram copies
 constexpr int kMatchPer = 4;                              // keys per thread per chunk
 constexpr int kMatchChunk = kMatchThreads * kMatchPer;
 
@@ -43,37 +53,64 @@ __device__ __forceinline__ uint32_t load_cc(const uint32_t* a) {  // coherent ac
     return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The chunk's keys: out-of-range slots get `valid` cleared.
+// The chunk's keys: out-of-range slots get `valid` cleared.  FORM: from the scores, left in
+// keys[b * max_cands + v]; otherwise read from there.
 struct ChunkKeys {
     uint32_t key[kMatchPer];
     bool valid[kMatchPer];
 };
-__device__ __forceinline__ ChunkKeys chunk_keys(const Prob& p, const float* scores, int reduce) {
-    __shared__ float red[kMatchThreads / kWave];
+template <bool FORM>
+__device__ __forceinline__ ChunkKeys chunk_keys(const Prob& p, const float* scores, int reduce,
+                                                uint32_t* keys) {
+    __shared__ float red[kSelThreads / kWave];
     const int b = blockIdx.x;
-    const int kb = k_begin(p, b);
     const int N = keys_of(p, b) - p.R;
-    const float sr = sample_reference<kMatchThreads>(p, scores, b, reduce, red);
+    uint32_t* kb = keys + (size_t)b * p.max_cands;
     ChunkKeys ck;
+    if (FORM) {
+        const float* sv = scores + k_begin(p, b) + p.R;
+        float x[kMatchPer];
+#pragma unroll
+        for (int j = 0; j < kMatchPer; ++j) {
+            const int v = blockIdx.y * kMatchChunk + j * kMatchThreads + threadIdx.x;
+            x[j] = v < N ? sv[v] : 0.f;
+        }
+        // The reference sum runs in the order of kSelThreads threads: occam_threshold's bits.
+        const float sr = sample_reference<kSelThreads>(p, scores, b, reduce, red);
+#pragma unroll
+        for (int j = 0; j < kMatchPer; ++j) {
+            const int v = blockIdx.y * kMatchChunk + j * kMatchThreads + threadIdx.x;
+            ck.valid[j] = v < N;
+            ck.key[j] = ck.valid[j] ? order_key(x[j] / sr) : 0u;
+            if (ck.valid[j]) kb[v] = ck.key[j];
+        }
+        return ck;
+    }
 #pragma unroll
     for (int j = 0; j < kMatchPer; ++j) {
         const int v = blockIdx.y * kMatchChunk + j * kMatchThreads + threadIdx.x;
         ck.valid[j] = v < N;
-        ck.key[j] = ck.valid[j] ? order_key(scores[kb + p.R + v] / sr) : 0u;
+        ck.key[j] = ck.valid[j] ? kb[v] : 0u;
     }
     return ck;
 }
 
-// True in every thread of the workgroup that finished last among the grid.
+// True in every thread of the workgroup that finished last among the grid.  The values
+// handed over are device-scope atomics: each wave waits until its own have completed.
 __device__ __forceinline__ bool last_workgroup(uint32_t* done) {
     __shared__ bool last;
-    __threadfence();
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
     __syncthreads();
     if (threadIdx.x == 0)
-        last = atomicAdd(done, 1u) == gridDim.x * gridDim.y - 1;
+        last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+               gridDim.x * gridDim.y - 1;
     __syncthreads();
-    if (last) __threadfence();
     return last;
+}
+
+// Relaxed device-scope atomics (performed where every XCD sees them).
+__device__ __forceinline__ void add_cc(uint32_t* a, uint32_t v) {
+    __hip_atomic_fetch_add(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ __launch_bounds__(kMatchThreads) void match_init_kernel(Prob p, float k_target,
@@ -101,45 +138,54 @@ __global__ __launch_bounds__(kMatchThreads) void match_init_kernel(Prob p, float
 
 template <int PASS>
 __global__ __launch_bounds__(kMatchThreads) void match_hist_kernel(
-    Prob p, const float* __restrict__ scores, int reduce, MatchState* st)
+    Prob p, const float* __restrict__ scores, int reduce, uint32_t* __restrict__ keys, MatchState* st)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t suffix[257];
+    __shared__ uint32_t hist[kMatchCopies * kMatchStride];
+    __shared__ uint32_t wave_sum[4];
     constexpr int shift = 24 - 8 * PASS;
     const int tid = threadIdx.x;
-    hist[tid] = 0;
+    for (int i = tid; i < kMatchCopies * kMatchStride; i += kMatchThreads) hist[i] = 0;
     const uint32_t mask = PASS == 0 ? 0u : ~0u << (32 - 8 * PASS);
     const uint32_t prefix = PASS == 0 ? 0u : st->prefix[PASS - 1];
     __syncthreads();
-    const ChunkKeys ck = chunk_keys(p, scores, reduce);
+    const ChunkKeys ck = chunk_keys<PASS == 0>(p, scores, reduce, keys);
+    uint32_t* mine = hist + (tid % kMatchCopies) * kMatchStride;
 #pragma unroll
     for (int j = 0; j < kMatchPer; ++j)
         if (ck.valid[j] && (ck.key[j] & mask) == prefix)
-            atomicAdd(&hist[(ck.key[j] >> shift) & 255u], 1u);
+            atomicAdd(&mine[(ck.key[j] >> shift) & 255u], 1u);
     __syncthreads();
-    if (hist[tid]) atomicAdd(&st->hist[PASS][tid], hist[tid]);
+    if (tid < 256) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int c = 0; c < kMatchCopies; ++c) n += hist[c * kMatchStride + tid];
+        if (n) add_cc(&st->hist[PASS][tid], n);
+    }
     if (!last_workgroup(&st->done[PASS])) return;
 
-    // Pick the digit: suffix[d] = keys in the group with digit >= d; the target of rank
-    // k (1 = largest) has the digit d with suffix[d + 1] < k <= suffix[d].
+    // Pick the digit: suffix(d) = keys in the group with digit >= d; the target of rank
+    // k (1 = largest) has the digit d with suffix(d + 1) < k <= suffix(d).  Thread t of the
+    // first four waves holds digit 255 - t, so that its suffix is a prefix over threads.
     const uint32_t k = load_cc(&st->rank[PASS]);
-    suffix[tid] = load_cc(&st->hist[PASS][tid]);
-    if (tid == 0) suffix[256] = 0;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t add = tid + off < 256 ? suffix[tid + off] : 0u;
-        __syncthreads();
-        suffix[tid] += add;
-        __syncthreads();
+    const uint32_t n = tid < 256 ? load_cc(&st->hist[PASS][255 - tid]) : 0u;
+    uint32_t inc = n;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off);
+        if ((tid & 63) >= off) inc += o;
     }
-    if (suffix[tid + 1] < k && k <= suffix[tid]) {
-        st->prefix[PASS] = prefix | ((uint32_t)tid << shift);
-        st->rank[PASS + 1] = k - suffix[tid + 1];
+    if (tid < 256 && (tid & 63) == 63) wave_sum[tid >> 6] = inc;
+    __syncthreads();
+    if (tid >= 256) return;
+    for (int w = 0; w < (tid >> 6); ++w) inc += wave_sum[w];
+    if (inc - n < k && k <= inc) {
+        st->prefix[PASS] = prefix | ((uint32_t)(255 - tid) << shift);
+        st->rank[PASS + 1] = k - (inc - n);
     }
 }
 
 __global__ __launch_bounds__(kMatchThreads) void match_count_kernel(
-    Prob p, const float* __restrict__ scores, int reduce, float k_target, MatchState* st,
+    Prob p, uint32_t* __restrict__ keys, float k_target, MatchState* st,
     float* __restrict__ lambda, float* __restrict__ mean_kept)
 {
     __shared__ uint32_t s_hi, s_lo, s_above, s_below;
@@ -147,7 +193,7 @@ __global__ __launch_bounds__(kMatchThreads) void match_count_kernel(
     if (tid == 0) { s_hi = 0; s_lo = 0; s_above = 0xFFFFFFFFu; s_below = 0u; }
     const uint32_t v1 = st->prefix[3];
     __syncthreads();
-    const ChunkKeys ck = chunk_keys(p, scores, reduce);
+    const ChunkKeys ck = chunk_keys<false>(p, nullptr, 0, keys);
     uint32_t hi = 0, lo = 0, above = 0xFFFFFFFFu, below = 0u;    // below holds key + 1
 #pragma unroll
     for (int j = 0; j < kMatchPer; ++j) {
@@ -158,16 +204,28 @@ __global__ __launch_bounds__(kMatchThreads) void match_count_kernel(
         if (key > v1) above = min(above, key);
         if (key < v1) below = max(below, key + 1u);
     }
-    if (hi) atomicAdd(&s_hi, hi);
-    if (lo) atomicAdd(&s_lo, lo);
-    if (above != 0xFFFFFFFFu) atomicMin(&s_above, above);
-    if (below) atomicMax(&s_below, below);
+    // One LDS atomic per wave.
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        hi += __shfl_xor(hi, off);
+        lo += __shfl_xor(lo, off);
+        above = min(above, (uint32_t)__shfl_xor(above, off));
+        below = max(below, (uint32_t)__shfl_xor(below, off));
+    }
+    if ((tid & 63) == 0) {
+        if (hi) atomicAdd(&s_hi, hi);
+        if (lo) atomicAdd(&s_lo, lo);
+        if (above != 0xFFFFFFFFu) atomicMin(&s_above, above);
+        if (below) atomicMax(&s_below, below);
+    }
     __syncthreads();
     if (tid == 0) {
-        if (s_hi) atomicAdd(&st->c_hi, s_hi);
-        if (s_lo) atomicAdd(&st->c_lo, s_lo);
-        if (s_above != 0xFFFFFFFFu) atomicMin(&st->v_above, s_above);
-        if (s_below) atomicMax(&st->v_below, s_below);
+        if (s_hi) add_cc(&st->c_hi, s_hi);
+        if (s_lo) add_cc(&st->c_lo, s_lo);
+        if (s_above != 0xFFFFFFFFu)
+            __hip_atomic_fetch_min(&st->v_above, s_above, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (s_below)
+            __hip_atomic_fetch_max(&st->v_below, s_below, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!last_workgroup(&st->done[4]) || tid != 0) return;
 
@@ -196,22 +254,23 @@ __global__ __launch_bounds__(kMatchThreads) void match_count_kernel(
 }
 
 hipError_t launch_match_lambda(const Prob& p, const float* scores, int reduce, float k_target,
-                               void* state, float* lambda, float* mean_kept, hipStream_t s)
+                               void* state, void* keys, float* lambda, float* mean_kept, hipStream_t s)
 {
     MatchState* st = static_cast<MatchState*>(state);
+    uint32_t* kk = static_cast<uint32_t*>(keys);
     const int chunks = (p.max_cands + kMatchChunk - 1) / kMatchChunk;
     const dim3 grid(p.B, chunks > 0 ? chunks : 1);
     const dim3 block(kMatchThreads);
     hipError_t e = launch(match_init_kernel, dim3(1), block, 0, s, p, k_target, st);
     if (e != hipSuccess) return e;
     if (chunks > 0) {
-        if ((e = launch(match_hist_kernel<0>, grid, block, 0, s, p, scores, reduce, st)) != hipSuccess ||
-            (e = launch(match_hist_kernel<1>, grid, block, 0, s, p, scores, reduce, st)) != hipSuccess ||
-            (e = launch(match_hist_kernel<2>, grid, block, 0, s, p, scores, reduce, st)) != hipSuccess ||
-            (e = launch(match_hist_kernel<3>, grid, block, 0, s, p, scores, reduce, st)) != hipSuccess)
+        if ((e = launch(match_hist_kernel<0>, grid, block, 0, s, p, scores, reduce, kk, st)) != hipSuccess ||
+            (e = launch(match_hist_kernel<1>, grid, block, 0, s, p, scores, reduce, kk, st)) != hipSuccess ||
+            (e = launch(match_hist_kernel<2>, grid, block, 0, s, p, scores, reduce, kk, st)) != hipSuccess ||
+            (e = launch(match_hist_kernel<3>, grid, block, 0, s, p, scores, reduce, kk, st)) != hipSuccess)
             return e;
     }
-    return launch(match_count_kernel, grid, block, 0, s, p, scores, reduce, k_target, st, lambda,
+    return launch(match_count_kernel, grid, block, 0, s, p, kk, k_target, st, lambda,
                   mean_kept);
 }
 

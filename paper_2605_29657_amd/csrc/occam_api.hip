@@ -490,7 +490,8 @@ occam_status occam_match_lambda(const occam_problem* problem, const float* score
         return OCCAM_ERR_INVALID_ARG;
     if ((st = check_ws(P, workspace, ws_bytes)) != OCCAM_OK) return st;
     return hip_ok(launch_match_lambda(P.p, scores, reduce, k_target,
-                                      ws_at<char>(workspace, P.off_match), lambda, mean_kept,
+                                      ws_at<char>(workspace, P.off_match),
+                                      ws_at<char>(workspace, P.off_slot), lambda, mean_kept,
                                       stream));
 }
 

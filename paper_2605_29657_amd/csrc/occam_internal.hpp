@@ -489,10 +489,11 @@ __device__ __forceinline__ void select_sample(const Prob& p, const float* scores
 // Launchers (defined in the .hip files).  Each returns the status of its own launches.
 hipError_t launch_select_topk(const Prob& p, const float* scores, int k_keep, int* slot,
                               int* count, hipStream_t s);
-// Selection state of budget matching, in the workspace.
+// Selection state of budget matching, in the workspace; `keys` takes the ratios' order keys,
+// B * max_cands words.
 constexpr size_t kMatchStateBytes = 8192;
 hipError_t launch_match_lambda(const Prob& p, const float* scores, int reduce, float k_target,
-                               void* state, float* lambda, float* mean_kept, hipStream_t s);
+                               void* state, void* keys, float* lambda, float* mean_kept, hipStream_t s);
 hipError_t launch_register_redirect(const Prob& p, int bf16, void* h, int width, long long stride,
                                     const int* channels, int n_channels, int reg_slot,
                                     hipStream_t s);
