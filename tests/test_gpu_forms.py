@@ -35,3 +35,37 @@ def test_statistics_units(stage, B, H, Hkv):
     T = [n + 2 for n in N] if stage == "mut" else [(53 * b + 2) % 290 + 2 for b in range(B)]
     sb = custom_stage(B=B, R=2, H=H, Hkv=Hkv, d=72, T=T, N=N, seed=300 + B, stage=stage)
     run_and_check(sb, 1.0)
+
+
+@pytest.mark.parametrize("H,d", [(12, 64), (20, 64), (16, 80)])
+@pytest.mark.parametrize("B,lo", [(3, 0), (40, 500)])
+def test_contiguous_run_one_row_form(H, d, B, lo):
+    # Key counts around the wave's run of rows and the workgroup's chunk (16 keys for three
+    # samples, 128 for forty), an empty sample among them.
+    N = [0, 1, 127, 126, 3][:B] + [lo + 13 * b for b in range(B - 5)]
+    sb = custom_stage(B=B, R=2, H=H, Hkv=H, d=d, T=[1] * B, N=N, seed=400 + H + B)
+    run_and_check(sb, 1.0)
+
+
+@pytest.mark.parametrize("N", [1, 63, 1024, 12287, 12288, 12289])
+@pytest.mark.parametrize("values", [0, 1, 7])
+def test_topk_edges(N, values):
+    # Around a wave's group, the workgroup and the LDS limit; all scores distinct, all equal,
+    # or seven levels.  Whole numbers: compared exactly with a stable sort.
+    import numpy as np
+    import torch
+    from paper_2605_29657_amd import occam
+    rng = np.random.default_rng(N + values)
+    s = rng.permutation(N).astype(np.float32) + 1 if values == 0 else (
+        rng.integers(0, values, N).astype(np.float32))
+    p = occam.Problem(1, 1, 1, 64, 1, rows=1, cands=N, dtype="f32")
+    ws = occam.workspace(p)
+    scores = torch.from_numpy(np.concatenate([[0.5], s]).astype(np.float32)).cuda()
+    for K in sorted({0, 1, N // 2, N}):
+        kept = torch.zeros(max(N, 1), dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+        offs = torch.zeros(2, dtype=torch.int32, device="cuda")
+        occam.select_topk(p, scores, K, kept, cnt, offs, ws)
+        want = np.sort(np.argsort(-s, kind="stable")[:K])
+        assert int(cnt[0]) == K and offs.tolist() == [0, K]
+        assert np.array_equal(kept[:K].cpu().numpy(), want)
