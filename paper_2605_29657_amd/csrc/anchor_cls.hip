@@ -14,8 +14,8 @@
 //             the chunk's per-head (max, sum exp) pair.
 // cls_stream / cls_stream_run  the same for H == Hkv with the query in registers:
 //             lanes own fixed 16-byte slots of the key rows (heads padded to a power
-//             of two of lanes), or, for 16 heads of 5-7 or 9 chunks, contiguous runs
-//             of four key rows with the per-(row, head) sums formed through LDS.
+//             of two of lanes), or, for the geometries of cls_run_rows, contiguous runs
+//             of key rows with the per-(row, head) sums formed through LDS.
 // cls_scores  grid (key chunk, sample): merges the per-chunk pairs of the
 //             sample into the softmax normaliser of every head (fixed order),
 //             then score(s) = (1/H) sum_h exp(l[s,h] - m_h) / z_h.
@@ -282,25 +282,26 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_kernel(
     }
 }
 
-// Streaming form for 16 heads whose chunk count NCK is not a power of two (d = 72 in
-// bfloat16: nine 16-byte chunks per head).  Padding a head to 16 lanes, as
-// cls_stream_kernel does, would have 7 of every 16 lanes reread a chunk; instead a wave
-// reads KB = 4 consecutive key rows as one contiguous run of 4 * 16 * NCK chunks, NCK
-// coalesced 1 KB loads per lane with no lane idle, and forms each chunk's partial dot
-// product.  The partials go to the wave's own LDS row, and lane L = (row r = L / 16,
-// head h = L % 16) adds the NCK partials of its (row, head) in chunk order, writes the
-// scaled logit and folds it into its online (max, sum exp) pair; the 16 pairs of a head
-// (4 waves x 4 rows) are merged in a fixed order at the end.
-template <bool BF16, int NCK>
+// Streaming form for head geometries whose padded lane slots do not fill whole wave loads or
+// waste many of them (cls_run_rows: 16 heads of 5-7, 9 or 10 chunks, 12 and 20 heads of 8).
+// Padding a nine-chunk head to 16 lanes, as cls_stream_kernel does, would have 7 of every 16
+// lanes reread a chunk; instead a wave reads KB consecutive key rows as one contiguous run
+// of KB * HH * NCK chunks, whole coalesced 1 KB loads with no lane idle, and forms each
+// chunk's partial dot product.  The partials go to the wave's own LDS row, and lane L =
+// (row r = L / HH, head h = L % HH) adds the NCK partials of its (row, head) in chunk order,
+// writes the scaled logit and folds it into its online (max, sum exp) pair; the 4 x KB pairs
+// of a head (4 waves x KB rows) are merged in a fixed order at the end.  Bound by HBM (64
+// samples of 256-4096 keys, 16 x 72: 344 MB in 66 us); a batch of 24 samples of 97-1200
+// keys with 12 heads of 64 took 27.4 us through cls_logits_kernel and its LDS table.
+template <bool BF16, int HH, int NCK, int KB>
 __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
     Prob p, const void* __restrict__ qv, const void* __restrict__ kv,
     float* __restrict__ logits, float2* __restrict__ stats, int kpw, int nchunks, Finish fin)
 {
     constexpr int CE = BF16 ? 8 : 4;                 // elements per 16-byte chunk
-    constexpr int HH = 16;                           // heads: 4 rows x 16 heads = 64 lanes
-    constexpr int KB = 4;                            // key rows per wave step
+    static_assert(KB * HH <= kWave, "one lane per (row, head)");
     constexpr int ROWC = HH * NCK;                   // 16-byte chunks per key row
-    constexpr int NJ = KB * ROWC / kWave;            // loads per lane per step (= NCK)
+    constexpr int NJ = KB * ROWC / kWave;            // loads per lane per step
     static_assert((KB * ROWC) % kWave == 0, "a run of KB rows fills whole wave loads");
     constexpr int NW = kClsThreads / kWave;
     __shared__ float part[NW][KB * ROWC];
@@ -335,6 +336,7 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
     }
 
     const int rr = lane / HH, hh = lane % HH;        // this lane's (row of the run, head)
+    const bool mine = KB * HH == kWave || rr < KB;
     float m = -INFINITY, z = 0.f;
     const u32x4* kbase = static_cast<const u32x4*>(kv) + ((size_t)k_begin(p, b) + s0) * ROWC;
     float* lout = logits + ((size_t)k_begin(p, b) + s0) * HH;
@@ -369,13 +371,15 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         float l = 0.f;
+        if (mine) {
 #pragma unroll
-        for (int sc = 0; sc < NCK; ++sc) l += prt[rr * ROWC + hh * NCK + sc];
+            for (int sc = 0; sc < NCK; ++sc) l += prt[rr * ROWC + hh * NCK + sc];
+        }
         l *= scale;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();             // reads done before the next step's writes
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (k0 + rr < nk) {
+        if (mine && k0 + rr < nk) {
             lout[(size_t)(k0 + rr) * HH + hh] = l;
             if (l > m) {
                 z = z * cls_exp<BF16>(m - l) + 1.f;
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
         }
     }
 
-    // Fixed-order merge of the 16 pairs of each head (waves, then rows; (-inf, 0) for a
+    // Fixed-order merge of the 4 x KB pairs of each head (waves, then rows; (-inf, 0) for a
     // row slot that saw no key).
     red_m[wave][lane] = m;
     red_z[wave][lane] = z;
@@ -567,15 +571,20 @@ hipError_t launch_cls_logits(const Prob& p, int bf16, const void* q, const void*
                              float* logits, float2* stats, int kpw, const Finish& fin,
                              hipStream_t s)
 {
-    if (bf16 && p.H == 16 && p.Hkv == 16 && (p.d == 72 || p.d == 40 || p.d == 48 || p.d == 56)) {
-        // 16 heads of 9 (5, 6, 7) chunks: contiguous runs of four key rows.
+    if (cls_run_rows(p.H, p.Hkv, p.d, bf16 ? 2 : 4)) {
         const int nchunks = (p.R + p.max_cands + kpw - 1) / kpw;
         const dim3 grid(nchunks, p.B), blk(kClsThreads);
+        const auto run = [&](auto kernel) {
+            return launch(kernel, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
+        };
+        if (p.H == 12) return run(cls_stream_run_kernel<true, 12, 8, 4>);
+        if (p.H == 20) return run(cls_stream_run_kernel<true, 20, 8, 2>);
         switch (p.d) {
-        case 40: return launch(cls_stream_run_kernel<true, 5>, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
-        case 48: return launch(cls_stream_run_kernel<true, 6>, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
-        case 56: return launch(cls_stream_run_kernel<true, 7>, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
-        default: return launch(cls_stream_run_kernel<true, 9>, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
+        case 40: return run(cls_stream_run_kernel<true, 16, 5, 4>);
+        case 48: return run(cls_stream_run_kernel<true, 16, 6, 4>);
+        case 56: return run(cls_stream_run_kernel<true, 16, 7, 4>);
+        case 72: return run(cls_stream_run_kernel<true, 16, 9, 4>);
+        default: return run(cls_stream_run_kernel<true, 16, 10, 4>);
         }
     }
     const int nc = cls_stream_nc(p.H, p.Hkv, p.d, bf16 ? 2 : 4);

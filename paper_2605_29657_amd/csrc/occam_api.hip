@@ -109,7 +109,8 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
                                              (size_t)P.kpw * H * NC + (size_t)P.kpw * H +
                                              2 * (size_t)kClsThreads);
         if (H > 64) return OCCAM_ERR_UNSUPPORTED;
-        if (!cls_stream_nc(H, x.num_kv_heads, d, bf16 ? 2 : 4) && smem > 65536)
+        if (!cls_stream_nc(H, x.num_kv_heads, d, bf16 ? 2 : 4) &&
+            !cls_run_rows(H, x.num_kv_heads, d, bf16 ? 2 : 4) && smem > 65536)
             return OCCAM_ERR_UNSUPPORTED;
         const long long nchunks = (R + (long long)max_cands + P.kpw - 1) / P.kpw;
         P.nchunks = nchunks > (1LL << 30) ? (1 << 30) : (int)nchunks;

@@ -364,6 +364,18 @@ inline int cls_stream_nc(int H, int Hkv, int d, int elem_bytes) {
     if (cpk % 64 != 0 || cpk / 64 > 4) return 0;
     return ncp;
 }
+// Key rows per wave step of the contiguous-run form (cls_stream_run_kernel; bf16, every
+// query head with its own key head), or 0 when it does not apply: a step fills whole 1 KB
+// wave loads and one lane serves each (row, head).  16 heads of a chunk count that is not a
+// power of two (padding would idle lanes), and 12 or 20 heads of 64 (their padded slots fill
+// no whole wave loads, so they had only the LDS-partials kernel).
+inline int cls_run_rows(int H, int Hkv, int d, int elem_bytes) {
+    if (elem_bytes != 2 || H != Hkv) return 0;
+    if (H == 16 && (d == 40 || d == 48 || d == 56 || d == 72 || d == 80)) return 4;
+    if (d == 64 && H == 12) return 4;
+    if (d == 64 && H == 20) return 2;
+    return 0;
+}
 constexpr int kClsStreamKeys = 128;    // keys per workgroup of the streaming form
 // Small batches: the streaming form halves its keys per workgroup (down to 16) until the
 // launch has this many workgroups (two per CU), so that a single image is read by many
@@ -371,7 +383,7 @@ constexpr int kClsStreamKeys = 128;    // keys per workgroup of the streaming fo
 constexpr int kClsMinWorkgroups = 512;
 
 inline int cls_keys_per_wg(int H, int Hkv, int d, int elem_bytes, int B = 0, long long keys = 0) {
-    if (cls_stream_nc(H, Hkv, d, elem_bytes)) {
+    if (cls_stream_nc(H, Hkv, d, elem_bytes) || cls_run_rows(H, Hkv, d, elem_bytes)) {
         int kpw = kClsStreamKeys;
         while (kpw > 16 && (long long)B * ((keys + kpw - 1) / kpw) < kClsMinWorkgroups) kpw /= 2;
         return kpw;
