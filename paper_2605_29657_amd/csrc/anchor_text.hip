@@ -571,7 +571,7 @@ __device__ __forceinline__ void score_task(
     u32x4* qt = reinterpret_cast<u32x4*>(smem_raw);                         // [2][QTILE]
     u32x4* kt = qt + 2 * QTILE + wave * KTILE;                              // this wave's keys
     float* l2t = reinterpret_cast<float*>(smem_raw + (2 * QTILE + NW * KTILE) * 16);  // [H][RB]
-    // Loop step hh works on head (hh + rot) mod H: a key row's head slices all sit at
+    // Loop step h works on head (h + rot) mod H: a key row's head slices all sit at
     // the same offset within 8 KB rows, so workgroups moving through the heads in step
     // would load the same memory channels at the same time.  Eight starting heads,
     // spread over the H heads, balance the channels as well as H of them do; with one
@@ -579,12 +579,18 @@ __device__ __forceinline__ void score_task(
     // the query tile and key slices they are reading.
     const int nrot = H < 8 ? H : 8;
     const int rot = (int)((unsigned)rot_id % (unsigned)nrot) * (H / nrot);
-    auto head_of = [&](int hh) {
-        const int hc = hh + rot;
-        return hc >= H ? hc - H : hc;
+    // The head of the current step and its key head, followed without a division per step.
+    int head = rot, kv = rot / group, in_group = rot % group;
+    auto advance = [&]() {
+        ++head;
+        if (++in_group == group) {
+            in_group = 0;
+            ++kv;
+        }
+        if (head == H) head = kv = in_group = 0;
     };
 
-    // Copy head hh's query tile (rows t0 .. t0 + RB - 1) into buffer buf.  Copy j of this
+    // Copy the head's query tile (rows t0 .. t0 + RB - 1) into buffer buf.  Copy j of this
     // wave fills units U = (wave*QCOPIES + j)*64 + lane: row t = U / NCH, the chunk
     // stored there is (U % NCH) ^ (t & SW).  Rows past T_b are clamped (their lse2 is
     // +inf, so they weigh exactly 0); the pad chunk past d (HALF) reads chunk 0
@@ -609,22 +615,20 @@ __device__ __forceinline__ void score_task(
     const char* qrows = reinterpret_cast<const char*>(q + ((size_t)qb + t0) * H * d);
     const char* ksample = reinterpret_cast<const char*>(k + (size_t)kb0 * Hkv * d);
     const uint32_t qt_lds = lds_addr(qt), kt_lds = lds_addr(kt);
-    auto copy_q = [&](int hh, int buf) {
-        const char* base = qrows + (size_t)head_of(hh) * d * 2;
+    auto copy_q = [&](int buf) {
+        const char* base = qrows + (size_t)head * d * 2;
 #pragma unroll
         for (int j = 0; j < QCOPIES; ++j)
             if ((QTILE / kWave) % NW == 0 || wave + NW * j < QTILE / kWave)
                 dma16_async(base, qoff[j],
                             qt_lds + (uint32_t)((buf * QTILE + (wave + NW * j) * kWave) * 16));
     };
-    auto copy_k = [&](int hh) {
-        const char* base = ksample + (size_t)(head_of(hh) / group) * d * 2;
+    auto copy_k = [&]() {
+        const char* base = ksample + (size_t)kv * d * 2;
 #pragma unroll
         for (int j = 0; j < KCOPIES; ++j)
             dma16_async(base, koff[j], kt_lds + (uint32_t)(j * kWave * 16));
     };
-    // Does step hh need other keys than step hh - 1 (grouped-query heads share theirs)?
-    auto new_keys = [&](int hh) { return group == 1 || head_of(hh) / group != head_of(hh - 1) / group; };
     // Byte offset of fragment (row lo of a 32-row block, chunk hi) for k-step 0; k-step kk
     // reads (frag ^ kk*32) with SW, (frag + kk*32) without.
     const uint32_t frag = (uint32_t)(lo * NCH + (hi ^ (lo & SW))) * 16u;
@@ -639,8 +643,8 @@ __device__ __forceinline__ void score_task(
         }
     };
 
-    copy_k(0);
-    copy_q(0, 0);
+    copy_k();
+    copy_q(0);
     const int nsb = min(NSB, (T - t0 + 31) >> 5);
     for (int i = tid; i < H * RB; i += kWave * NW) {
         const int hh = i / RB, t = t0 + (i % RB);
@@ -668,12 +672,15 @@ __device__ __forceinline__ void score_task(
         // key fragments and synchronise.
         const int buf = h & 1;
         const bool more = h + 1 < H;
-        const bool nk = more && new_keys(h + 1);
-        if (more) copy_q(h + 1, buf ^ 1);
-        if (nk) copy_k(h + 1);
+        const float* l2h = l2t + head * RB + lo;
+        const int kv_now = kv;
+        advance();
+        // Grouped-query heads share their keys.
+        const bool nk = more && (group == 1 || kv != kv_now);
+        if (more) copy_q(buf ^ 1);
+        if (nk) copy_k();
         if (wactive) {
             const char* qtile = reinterpret_cast<const char*>(qt) + buf * QTILE * 16;
-            const float* l2h = l2t + head_of(h) * RB + lo;
             auto chain = [&](int sp) {
                 f32x16 acc = {};
 #pragma unroll
@@ -766,13 +773,16 @@ __device__ __forceinline__ void score_task(
 // With fin.done, the last workgroup of each sample forms its scores from the row blocks'
 // partials (text_rows_combine's arithmetic) and, with fin.select, applies the threshold
 // and the compaction (select_kernel's arithmetic).
-template <int DS, bool HALF, int NW, int NSB, bool FULL>
-__global__ __launch_bounds__(NW * kWave, 2) void text_score_kernel(
+// WIDE: eight waves and 128-row blocks that are all full, else four waves and 64-row blocks
+// (score_form).
+template <int DS, bool HALF, bool WIDE>
+__global__ __launch_bounds__((WIDE ? 8 : 4) * kWave, 2) void text_score_kernel(
     Prob p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const float* __restrict__ lse, int lse_natural, float* __restrict__ scores,
     float* __restrict__ part, Finish fin)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+    constexpr int NW = WIDE ? 8 : 4, NSB = WIDE ? 4 : 2;
     constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB, NT = NW * kWave;
     const int nchunk = (p.R + p.max_cands + KPW - 1) / KPW;
     const int nrb = (p.max_rows + RB - 1) / RB;
@@ -801,7 +811,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void text_score_kernel(
     // XCD's L2.  A start per key chunk instead fetched 1062 MB per launch at the
     // LLaVA-NeXT shape and 3586 MB on the ragged Qwen3-VL batch; per XCD, 807 and 2654 MB,
     // ~1 % faster.
-    score_task<DS, HALF, NW, NSB, FULL>(p, q, k, lse, lse_natural, scores, part, b, c, rb,
+    score_task<DS, HALF, NW, NSB, WIDE>(p, q, k, lse, lse_natural, scores, part, b, c, rb,
                                       (int)blockIdx.x, smem_raw, fin.done != nullptr);
     if (!fin.done) return;
     const int S = keys_of(p, b), T = rows_of(p, b);
@@ -978,23 +988,23 @@ __global__ __launch_bounds__(256) void text_colsum_reduce_kernel(Prob p, const f
     scores[k_begin(p, b) + s] = T > 0 ? acc * (1.f / ((float)p.H * (float)T)) : 0.f;
 }
 
-template <int DS, bool HALF, int NW, int NSB, bool FULL>
+template <int DS, bool HALF, bool WIDE>
 static hipError_t score_launch(const Prob& p, const void* q, const void* k, const float* lse,
                                int lse_natural, float* scores, float* part, const Finish& fin,
                                hipStream_t s) {
-    constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB;
+    constexpr int NW = WIDE ? 8 : 4, RB = WIDE ? 128 : 64, KPW = kTxtKeysPerWave * NW;
     size_t smem = score_smem(ScoreForm{NW, RB}, p.H, DS * 16);
     if (fin.select) smem = std::max(smem, 128 + select_lds_bytes(p.R, p.max_cands));
     // The tiles need more than the default 64 KB of dynamic LDS: raise the limit (once per
     // device).
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t attr = allow_lds(
-        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, NW, NSB, FULL>), (int)kScoreSmemMax,
+        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, WIDE>), (int)kScoreSmemMax,
         lds_set);
     if (attr != hipSuccess) return attr;
     const int nrb = (p.max_rows + RB - 1) / RB;
     dim3 grid((p.R + p.max_cands + KPW - 1) / KPW * nrb * p.B);
-    const hipError_t e = launch(text_score_kernel<DS, HALF, NW, NSB, FULL>, grid, dim3(NW * kWave), smem, s,
+    const hipError_t e = launch(text_score_kernel<DS, HALF, WIDE>, grid, dim3(NW * kWave), smem, s,
                                 p, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                                 lse, lse_natural, scores, nrb > 1 ? part : nullptr, fin);
     if (e != hipSuccess || nrb == 1 || fin.done) return e;
@@ -1007,8 +1017,8 @@ static hipError_t score_ds(const Prob& p, const void* q, const void* k, const fl
                            int lse_natural, float* scores, float* part, const Finish& fin,
                            hipStream_t s) {
     if (score_form(p).waves == 8)
-        return score_launch<DS, HALF, 8, 4, true>(p, q, k, lse, lse_natural, scores, part, fin, s);
-    return score_launch<DS, HALF, 4, 2, false>(p, q, k, lse, lse_natural, scores, part, fin, s);
+        return score_launch<DS, HALF, true>(p, q, k, lse, lse_natural, scores, part, fin, s);
+    return score_launch<DS, HALF, false>(p, q, k, lse, lse_natural, scores, part, fin, s);
 }
 
 // d = 16*DS (HALF = false) or 16*DS - 8 (HALF = true), d <= 128.
