@@ -991,7 +991,7 @@ __global__ __launch_bounds__(256) void text_colsum_reduce_kernel(Prob p, const f
 template <int DS, bool HALF, bool WIDE>
 static hipError_t score_launch(const Prob& p, const void* q, const void* k, const float* lse,
                                int lse_natural, float* scores, float* part, const Finish& fin,
-                               hipStream_t s) {
+                               bool leave_blocks, hipStream_t s) {
     constexpr int NW = WIDE ? 8 : 4, RB = WIDE ? 128 : 64, KPW = kTxtKeysPerWave * NW;
     size_t smem = score_smem(ScoreForm{NW, RB}, p.H, DS * 16);
     if (fin.select) smem = std::max(smem, 128 + select_lds_bytes(p.R, p.max_cands));
@@ -1007,7 +1007,7 @@ static hipError_t score_launch(const Prob& p, const void* q, const void* k, cons
     const hipError_t e = launch(text_score_kernel<DS, HALF, WIDE>, grid, dim3(NW * kWave), smem, s,
                                 p, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                                 lse, lse_natural, scores, nrb > 1 ? part : nullptr, fin);
-    if (e != hipSuccess || nrb == 1 || fin.done) return e;
+    if (e != hipSuccess || nrb == 1 || fin.done || leave_blocks) return e;
     dim3 cgrid((p.R + p.max_cands + 255) / 256, p.B);
     return launch(text_rows_combine_kernel, cgrid, dim3(256), 0, s, p, RB, part, scores);
 }
@@ -1015,10 +1015,10 @@ static hipError_t score_launch(const Prob& p, const void* q, const void* k, cons
 template <int DS, bool HALF>
 static hipError_t score_ds(const Prob& p, const void* q, const void* k, const float* lse,
                            int lse_natural, float* scores, float* part, const Finish& fin,
-                           hipStream_t s) {
+                           bool leave_blocks, hipStream_t s) {
     if (score_form(p).waves == 8)
-        return score_launch<DS, HALF, true>(p, q, k, lse, lse_natural, scores, part, fin, s);
-    return score_launch<DS, HALF, false>(p, q, k, lse, lse_natural, scores, part, fin, s);
+        return score_launch<DS, HALF, true>(p, q, k, lse, lse_natural, scores, part, fin, leave_blocks, s);
+    return score_launch<DS, HALF, false>(p, q, k, lse, lse_natural, scores, part, fin, leave_blocks, s);
 }
 
 // d = 16*DS (HALF = false) or 16*DS - 8 (HALF = true), d <= 128.
@@ -1042,8 +1042,8 @@ hipError_t launch_text_stats(const Prob& p, const void* q, const void* k, float*
 
 hipError_t launch_text_score(const Prob& p, const void* q, const void* k, const float* lse,
                              int lse_natural, float* scores, float* part, const Finish& fin,
-                             hipStream_t s) {
-    OCCAM_D_SWITCH(score_ds, p, q, k, lse, lse_natural, scores, part, fin, s)
+                             bool leave_blocks, hipStream_t s) {
+    OCCAM_D_SWITCH(score_ds, p, q, k, lse, lse_natural, scores, part, fin, leave_blocks, s)
 }
 
 static hipError_t colsum_any(const Prob& p, const void* q, const void* k, const float* lse,

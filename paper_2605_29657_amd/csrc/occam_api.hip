@@ -187,7 +187,8 @@ inline occam_status hip_ok(hipError_t e) { return e == hipSuccess ? OCCAM_OK : O
 // then also combines its row blocks in the scoring kernel.
 occam_status run_score(const Plan& P, const void* q, const void* k, const float* row_lse,
                        float* scores, void* ws, hipStream_t s, const Finish* sel = nullptr,
-                       int* selected = nullptr, ChunkLists* lists = nullptr) {
+                       int* selected = nullptr, ChunkLists* lists = nullptr,
+                       const float** blocks = nullptr) {
     Finish fin{};
     if (selected) *selected = 0;
     if (P.text) {
@@ -229,7 +230,11 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
         const int natural = row_lse ? 1 : 0;
         float* part = ws_at<float>(ws, P.off_part);
         if (P.p.mean_rows) return hip_ok(launch_text_colsum(P.p, q, k, lse, natural, part, scores, s));
-        return hip_ok(launch_text_score(P.p, q, k, lse, natural, scores, part, fin, s));
+        // No counters with a caller normaliser: the select that must follow a prune's scoring
+        // combines the row blocks.
+        const bool leave = blocks && !fin.done && P.p.max_rows > score_form(P.p).rows;
+        if (leave) *blocks = part;
+        return hip_ok(launch_text_score(P.p, q, k, lse, natural, scores, part, fin, leave, s));
     }
     float* logits = ws_at<float>(ws, P.off_logits);
     float2* stats = ws_at<float2>(ws, P.off_stats);
@@ -295,11 +300,13 @@ occam_status run_prune(const Plan& P, const void* q, const void* k, const float*
     sel.count = kept_count;
     int selected = 0;
     ChunkLists lists{};
-    if ((st = run_score(P, q, k, row_lse, sc, workspace, stream, &sel, &selected, &lists)) !=
-        OCCAM_OK)
+    const float* blocks = nullptr;
+    if ((st = run_score(P, q, k, row_lse, sc, workspace, stream, &sel, &selected, &lists,
+                        &blocks)) != OCCAM_OK)
         return st;
     if (!selected) {
-        st = hip_ok(launch_select(P.p, sc, nullptr, 1, lambda, reduce, tu, slot, kept_count, stream));
+        st = hip_ok(launch_select(P.p, sc, blocks, score_form(P.p).rows, nullptr, 1, lambda, reduce,
+                                  tu, slot, kept_count, stream));
         if (st != OCCAM_OK) return st;
     }
     return hip_ok(launch_pack_gather(P.p, slot, kept_count, index_map, kept_idx, kept_offsets,
@@ -401,7 +408,9 @@ occam_status occam_select(const occam_problem* problem, const float* scores, con
         return OCCAM_ERR_INVALID_ARG;
     if ((st = check_ws(P, workspace, ws_bytes)) != OCCAM_OK) return st;
     int* slot = ws_at<int>(workspace, P.off_slot);
-    st = hip_ok(launch_select(P.p, scores, tau, 0, 0.f, 0, nullptr, slot, kept_count, stream));
+    // (Without row blocks the scores are only read.)
+    st = hip_ok(launch_select(P.p, const_cast<float*>(scores), nullptr, 0, tau, 0, 0.f, 0, nullptr,
+                              slot, kept_count, stream));
     if (st != OCCAM_OK) return st;
     RowTensors none;
     memset(&none, 0, sizeof none);

@@ -526,15 +526,18 @@ hipError_t launch_text_colsum(const Prob& p, const void* q, const void* k, const
 // Max-over-rows scoring; with several 128-row blocks, per-block partials go to part
 // [B][ceil(max_rows/128)][R + max_cands] and a combine kernel forms the scores.
 // With fin.done the row-block combine (and with fin.select the threshold and the
-// compaction) run in each sample's last workgroup; without it text_rows_combine follows.
+// compaction) run in each sample's last workgroup; without it text_rows_combine follows,
+// unless leave_blocks (launch_select then combines them).
 hipError_t launch_text_score(const Prob& p, const void* q, const void* k, const float* lse,
                              int lse_natural, float* scores, float* part, const Finish& fin,
-                             hipStream_t s);
+                             bool leave_blocks, hipStream_t s);
 hipError_t launch_threshold(const Prob& p, const float* scores, float lambda, int reduce,
                             float* tau, hipStream_t s);
-hipError_t launch_select(const Prob& p, const float* scores, const float* tau, int fuse_tau,
-                         float lambda, int reduce, float* tau_out, int* slot, int* count,
-                         hipStream_t s);
+// part (nullable): row blocks of rb_rows rows left by launch_text_score, from which the
+// scores are formed (and stored) first.
+hipError_t launch_select(const Prob& p, float* scores, const float* part, int rb_rows,
+                         const float* tau, int fuse_tau, float lambda, int reduce, float* tau_out,
+                         int* slot, int* count, hipStream_t s);
 // Survivors from the per-chunk lists of the one-row scoring kernel (chunk_cnt != null)
 // or from slot[co_b + i] (select); counts per sample in count[B] either way.
 struct ChunkLists {

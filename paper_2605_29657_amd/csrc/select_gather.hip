@@ -12,7 +12,9 @@
 //              ranges, and a second walk writes each survivor's candidate-local
 //              index, ascending, at its position (mbcnt below the lane) in the
 //              sample's slot of the workspace (slot[co_b + i]).  Optionally computes
-//              tau first (fused threshold of occam_prune).  The same compaction runs
+//              tau first (fused threshold of occam_prune), and before that the scores from
+//              the row blocks' partials (occam_prune with a caller normaliser: a
+//              combine launch before it cost the chained batch 92.5 against 90.8 us).  The same compaction runs
 //              in the last workgroup of each sample of the Stage II scoring kernel.
 // pack_gather  grid (G, sample): every wave forms its sample's packed offset
 //              (exclusive sum of the counts before it, with shuffles: no
@@ -43,9 +45,9 @@ __global__ __launch_bounds__(kSelThreads) void threshold_mean_kernel(
 }
 
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(
-    Prob p, const float* __restrict__ scores, const float* __restrict__ tau_in, int fuse_tau,
-    float lambda, int reduce, float* __restrict__ tau_out, int* __restrict__ slot,
-    int* __restrict__ count)
+    Prob p, float* scores, const float* __restrict__ part, int rb_rows,
+    const float* __restrict__ tau_in, int fuse_tau, float lambda, int reduce,
+    float* __restrict__ tau_out, int* __restrict__ slot, int* __restrict__ count)
 {
     // The fused threshold's reference sum runs in the order of kSelThreads threads, the
     // same bits as occam_threshold and budget matching.
@@ -53,6 +55,36 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(
     __shared__ float red[kSelThreads / kWave];
     __shared__ float tau_s;
     const int b = blockIdx.x;
+    if (part) {
+        // text_rows_combine's arithmetic, four keys' blocks in flight per thread.
+        constexpr int U = 4;
+        const int S = keys_of(p, b), T = rows_of(p, b);
+        const int nrb_max = (p.max_rows + rb_rows - 1) / rb_rows, nrb = (T + rb_rows - 1) / rb_rows;
+        const size_t smax = (size_t)(p.R + p.max_cands);
+        const float* pb = part + (size_t)b * nrb_max * smax;
+        float* out = scores + k_begin(p, b);
+        const float inv_reg = 1.f / ((float)p.H * (float)T), inv_vis = 1.f / (float)p.H;
+        for (int s0 = threadIdx.x; s0 < S; s0 += U * kSelectThreads) {
+            float v[U] = {0.f, 0.f, 0.f, 0.f};
+            for (int r = 0; r < nrb; ++r) {
+                float x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int s = s0 + u * kSelectThreads;
+                    x[u] = s < S ? pb[(size_t)r * smax + s] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    v[u] = s0 + u * kSelectThreads < p.R ? v[u] + x[u] : fmaxf(v[u], x[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int s = s0 + u * kSelectThreads;
+                if (s < S) out[s] = v[u] * (s < p.R ? inv_reg : inv_vis);
+            }
+        }
+        __syncthreads();
+    }
     if (fuse_tau) {
         const float t = lambda * sample_reference<kSelThreads>(p, scores, b, reduce, red);
         if (threadIdx.x == 0) {
@@ -212,12 +244,12 @@ hipError_t launch_threshold(const Prob& p, const float* scores, float lambda, in
                   reduce, tau);
 }
 
-hipError_t launch_select(const Prob& p, const float* scores, const float* tau, int fuse_tau,
-                         float lambda, int reduce, float* tau_out, int* slot, int* count,
-                         hipStream_t s)
+hipError_t launch_select(const Prob& p, float* scores, const float* part, int rb_rows,
+                         const float* tau, int fuse_tau, float lambda, int reduce, float* tau_out,
+                         int* slot, int* count, hipStream_t s)
 {
-    return launch(select_kernel, dim3(p.B), dim3(kSelectThreads), 0, s, p, scores, tau, fuse_tau,
-                  lambda, reduce, tau_out, slot, count);
+    return launch(select_kernel, dim3(p.B), dim3(kSelectThreads), 0, s, p, scores, part, rb_rows,
+                  tau, fuse_tau, lambda, reduce, tau_out, slot, count);
 }
 
 hipError_t launch_pack_gather(const Prob& p, const int* slot, const int* count,

@@ -69,3 +69,36 @@ def test_topk_edges(N, values):
         want = np.sort(np.argsort(-s, kind="stable")[:K])
         assert int(cnt[0]) == K and offs.tolist() == [0, K]
         assert np.array_equal(kept[:K].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("T", [64, 65, 128, 300])
+def test_caller_normaliser_blocks_combined_in_the_select(T):
+    # With a caller normaliser the fused prune combines the row blocks in its select: the
+    # unfused calls' scores, thresholds and survivors bit for bit.
+    import numpy as np
+    import torch
+    from paper_2605_29657_amd import occam
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    B, H, Hkv, d, R, N = 3, 4, 2, 64, 3, 700
+    keys = B * (R + N)
+    q = torch.randn(B * T, H, d, generator=gen, device="cuda").bfloat16()
+    k = torch.randn(keys, Hkv, d, generator=gen, device="cuda").bfloat16()
+    lse = 7.0 + torch.rand(B * T, H, generator=gen, device="cuda")
+    p = occam.Problem(B, H, Hkv, d, R, rows=T, cands=N)
+    ws = occam.workspace(p)
+    got = []
+    for fused in (True, False):
+        s, tau = torch.zeros(keys, device="cuda"), torch.zeros(B, device="cuda")
+        idx = torch.zeros(B * N, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(B, dtype=torch.int32, device="cuda")
+        off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+        if fused:
+            occam.prune(p, q, k, 1.5, idx, cnt, off, ws, scores=s, tau=tau, row_lse=lse)
+        else:
+            occam.score(p, q, k, s, ws, row_lse=lse)
+            occam.threshold(p, s, 1.5, occam.REG_MEAN, tau)
+            occam.select(p, s, tau, idx, cnt, off, ws)
+        got.append([x.cpu().numpy() for x in (s, tau, idx, cnt, off)])
+    assert 0 < got[0][3].sum() < B * N
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
