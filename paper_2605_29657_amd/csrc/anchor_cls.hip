@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_kernel(
 }
 
 // Streaming form for head geometries whose padded lane slots do not fill whole wave loads or
-// waste many of them (cls_run_rows: 16 heads of 5-7, 9 or 10 chunks, 12 and 20 heads of 8).
+// waste many of them (cls_run_rows: 16 heads of 5-7 or 9 chunks, 12 and 20 heads of 8).
 // Padding a nine-chunk head to 16 lanes, as cls_stream_kernel does, would have 7 of every 16
 // lanes reread a chunk; instead a wave reads KB consecutive key rows as one contiguous run
 // of KB * HH * NCK chunks, whole coalesced 1 KB loads with no lane idle, and forms each
@@ -583,8 +583,7 @@ hipError_t launch_cls_logits(const Prob& p, int bf16, const void* q, const void*
         case 40: return run(cls_stream_run_kernel<true, 16, 5, 4>);
         case 48: return run(cls_stream_run_kernel<true, 16, 6, 4>);
         case 56: return run(cls_stream_run_kernel<true, 16, 7, 4>);
-        case 72: return run(cls_stream_run_kernel<true, 16, 9, 4>);
-        default: return run(cls_stream_run_kernel<true, 16, 10, 4>);
+        default: return run(cls_stream_run_kernel<true, 16, 9, 4>);
         }
     }
     const int nc = cls_stream_nc(p.H, p.Hkv, p.d, bf16 ? 2 : 4);

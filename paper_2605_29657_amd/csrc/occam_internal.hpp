@@ -366,12 +366,13 @@ inline int cls_stream_nc(int H, int Hkv, int d, int elem_bytes) {
 }
 // Key rows per wave step of the contiguous-run form (cls_stream_run_kernel; bf16, every
 // query head with its own key head), or 0 when it does not apply: a step fills whole 1 KB
-// wave loads and one lane serves each (row, head).  16 heads of a chunk count that is not a
-// power of two (padding would idle lanes), and 12 or 20 heads of 64 (their padded slots fill
+// wave loads and one lane serves each (row, head).  16 heads of 5-7 or 9 chunks (padding
+// would idle lanes; ten chunks gain 7 % on large batches but lose 10 % on one image, and stay
+// with the padded form), and 12 or 20 heads of 64 (their padded slots fill
 // no whole wave loads, so they had only the LDS-partials kernel).
 inline int cls_run_rows(int H, int Hkv, int d, int elem_bytes) {
     if (elem_bytes != 2 || H != Hkv) return 0;
-    if (H == 16 && (d == 40 || d == 48 || d == 56 || d == 72 || d == 80)) return 4;
+    if (H == 16 && (d == 40 || d == 48 || d == 56 || d == 72)) return 4;
     if (d == 64 && H == 12) return 4;
     if (d == 64 && H == 20) return 2;
     return 0;

@@ -86,6 +86,10 @@ def test_caller_normaliser_blocks_combined_in_the_select(T):
     lse = 7.0 + torch.rand(B * T, H, generator=gen, device="cuda")
     p = occam.Problem(B, H, Hkv, d, R, rows=T, cands=N)
     ws = occam.workspace(p)
+    first = torch.zeros(keys, device="cuda")
+    occam.score(p, q, k, first, ws, row_lse=lse)
+    f = first.cpu().numpy().reshape(B, R + N)
+    lam = float(np.median(f[:, R:] / f[:, :R].mean(1, keepdims=True)))
     got = []
     for fused in (True, False):
         s, tau = torch.zeros(keys, device="cuda"), torch.zeros(B, device="cuda")
@@ -93,10 +97,10 @@ def test_caller_normaliser_blocks_combined_in_the_select(T):
         cnt = torch.zeros(B, dtype=torch.int32, device="cuda")
         off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
         if fused:
-            occam.prune(p, q, k, 1.5, idx, cnt, off, ws, scores=s, tau=tau, row_lse=lse)
+            occam.prune(p, q, k, lam, idx, cnt, off, ws, scores=s, tau=tau, row_lse=lse)
         else:
             occam.score(p, q, k, s, ws, row_lse=lse)
-            occam.threshold(p, s, 1.5, occam.REG_MEAN, tau)
+            occam.threshold(p, s, lam, occam.REG_MEAN, tau)
             occam.select(p, s, tau, idx, cnt, off, ws)
         got.append([x.cpu().numpy() for x in (s, tau, idx, cnt, off)])
     assert 0 < got[0][3].sum() < B * N
