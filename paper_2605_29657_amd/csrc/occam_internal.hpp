@@ -299,12 +299,16 @@ inline size_t score_smem(const ScoreForm& f, int H, int d16) {
 // Elsewhere the narrow form's finer tasks win: ragged grouped-query batch (64 samples of
 // 256-4096 keys and 16-512 rows) 427 us against 449 and 470; 32 chained samples of 64-1100
 // keys x 128 rows 70 against 93 and 80; one image (2880 keys x 128 rows) 47, 79 and 63.
+// With key offsets the tasks are counted by the bound max_cands, which a batch of mixed
+// lengths fills about half, so the line lies higher.  Whole call, samples of 64-1100 keys x
+// 128 rows with the caller's normaliser, wide / narrow / former: 40 samples (200 tasks by the
+// bound) 103, 82 and 91 us; 52 (260) 106, 86 and 94; 64 (320) 110, 138 and 133.
 inline ScoreForm score_form(const Prob& p) {
     const ScoreForm wide{8, 128}, narrow{4, 64};
     const long long kpw = (long long)wide.waves * kTxtKeysPerWave;
     const long long tasks = (long long)p.B * ((p.R + (long long)p.max_cands + kpw - 1) / kpw) *
                             (p.max_rows / wide.rows);
-    return !p.q_off && p.rows % wide.rows == 0 && tasks >= 256 &&
+    return !p.q_off && p.rows % wide.rows == 0 && tasks >= (p.k_off ? 300 : 256) &&
                    score_smem(wide, p.H, (p.d + 15) / 16 * 16) <= kScoreSmemMax
                ? wide
                : narrow;

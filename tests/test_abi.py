@@ -280,3 +280,24 @@ def test_prune_noalloc_validation(L):
     assert call(big, args()) == occam.ERR_WORKSPACE
     assert L.occam_prune_noalloc(None, FAKE, FAKE, None, 1.0, 0, None, 0, None, None, None, FAKE,
                                  FAKE, FAKE, None) == occam.ERR_INVALID_ARG
+
+
+def text_ws(B, H, T, N, R, blocks, max_rows=None, splits=1):
+    """Workspace of a multi-row max problem whose scoring leaves `blocks` row-block partials
+    per sample (0: it writes the scores itself), its statistics `splits` normaliser tables."""
+    up = lambda n: (n + 255) // 256 * 256
+    block, nrb = B * (R + N) * 4, (T + 127) // 128
+    part = up(nrb * block if nrb > 1 else 0)
+    if blocks > 1:
+        part += up((blocks - (nrb if nrb > 1 else 0)) * block)
+    return (up(splits * B * T * H * 4) + part + up(B * 4) + up(block) + up(B * 4) + up(B * N * 4) +
+            8192)
+
+
+def test_scoring_form_with_key_offsets(L):
+    # The wide scoring form (128-row blocks) is chosen by the bound on the keys; a ragged batch
+    # fills the bound about half, so it needs more of it than a uniform one.
+    for B, ragged, blocks in ((52, True, 2), (64, True, 1), (52, False, 1), (51, False, 2)):
+        p = occam.Problem(B, 32, 32, 128, 4, rows=128, cands=1100,
+                          key_offsets=FAKE if ragged else None, max_cands=1100)
+        assert ws_size(p) == text_ws(B, 32, 128, 1100, 4, blocks), (B, ragged)

@@ -26,6 +26,17 @@ def test_wide_scoring_form(d, Hkv, N):
     run_and_check(sb, 1.0)
 
 
+@pytest.mark.parametrize("T", [128, 256])
+def test_wide_scoring_form_with_key_offsets(T):
+    # Ragged keys, uniform rows: 330 or 333 wide tasks by the bound, decoded from the offsets
+    # in a 512-thread workgroup; a full sample, a chunk of one key, less than a wave's keys,
+    # and none.
+    B = 5 if T == 256 else 9
+    N = [8190 if T == 256 else 9300, 30, 0, 255, 4000, 511, 0, 64, 1][:B]
+    sb = custom_stage(B=B, R=2, H=2, Hkv=1, d=128, T=[T] * B, N=N, seed=250 + T)
+    run_and_check(sb, 1.0, ragged=True, row_offsets=False)
+
+
 @pytest.mark.parametrize("stage", ["txt", "mut"])
 @pytest.mark.parametrize("B,H,Hkv", [(9, 7, 7), (8, 8, 8), (11, 12, 6)])
 def test_statistics_units(stage, B, H, Hkv):
