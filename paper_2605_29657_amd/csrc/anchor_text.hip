@@ -31,11 +31,12 @@
 //             writes per-(row block, head) column sums for mutual scoring (Eq.
 //             mutual_scoring, every key takes the mean over rows);
 //             text_colsum_reduce adds them in a fixed order.
-// text_score  one workgroup per (sample, block of keys, row block): four waves and 64 rows,
-//             or eight waves and 128 rows (score_form).  Each wave owns 32 keys.  For
+// text_score  one workgroup per (sample, block of keys, row block): four waves and 64 or 128
+//             rows, or eight waves and 128 rows (score_form).  Each wave owns 32 keys.  For
 //             every head the query tile (double-buffered) and the wave's keys are copied
 //             global -> LDS in whole lines one head ahead, and the key fragments then go
-//             to registers, while p = 2^(x - lse2) of the
+//             to registers (or the keys are loaded into them directly), while
+//             p = 2^(x - lse2) of the
 //             current head is accumulated over heads per (key, row); the workgroups
 //             of one XCD walk the heads from the same start.  Afterwards the row
 //             reduction of Eq. text_scoring is applied: max over rows for visual
@@ -522,8 +523,8 @@ __device__ void ragged_score_task(const Prob& p, int id, int kpw, int rb, int* s
 // One scoring task: keys [KPW c, KPW c + KPW) of sample b (KPW = 32 NW) against its row
 // block rb, by NW waves.  cc_out: the scores / partials are read later in the same launch
 // by another workgroup, so they are written with device-coherent stores.  rot_id picks the
-// starting head (rot_id % 8 of 8 heads spread over H).
-template <int DS, bool HALF, int NW, int NSB, bool FULL>
+// starting head (rot_id % 8 of 8 heads spread over H).  KLDS: the keys reach LDS first.
+template <int DS, bool HALF, int NW, int NSB, bool KLDS>
 __device__ __forceinline__ void score_task(
     const Prob& p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const float* __restrict__ lse, int lse_natural, float* __restrict__ scores,
@@ -536,20 +537,21 @@ __device__ __forceinline__ void score_task(
     // operations per 32 x 32 x 128 block): a probe of that block with operands from LDS
     // takes ~250 ns per SIMD on random data (206-219 ns without the LDS reads, 160 ns on
     // constant data, i.e. the card's power limit shows); the video batch's 1025 blocks per
-    // SIMD take 440 ns each here, 500 before.  Keys loaded straight into the MFMA layout
-    // (32 lines touched per 1 KB load, ~58 cycles each) were the largest part of the load
-    // path before; whole-line copies take 16.
+    // SIMD take 440 ns each here, 500 with the keys loaded straight into the MFMA layout
+    // (32 lines touched per 1 KB load, ~58 cycles each; whole-line copies take 16).
     //
     // Both operands of a head reach LDS by whole-line global -> LDS copies, row-major with
     // an XOR swizzle: chunk c of row t sits in unit t*NCH + (c ^ (t & SW)), SW = NCH - 1
     // when NCH is a power of two (else 0).  The query tile is shared by the waves and
     // double-buffered (one barrier per head); a wave's 32 keys go to an area of its own,
     // from which it takes its fragments into registers before the next head's copy starts,
-    // so one buffer is enough.
+    // so one buffer is enough.  Without KLDS the fragments of the next head are loaded into
+    // a second set of registers instead.
+    constexpr bool FULL = NSB == 4;              // all sub-blocks, rows past T_b weigh 0
     constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB;
     constexpr int NCH = 2 * DS;                                   // 16-byte chunks per row
     constexpr int QTILE = RB * NCH;                         // 16-byte units per tile
-    constexpr int KTILE = kTxtKeysPerWave * NCH;                  // units of one wave's keys
+    constexpr int KTILE = KLDS ? kTxtKeysPerWave * NCH : 0;       // units of one wave's keys
     constexpr int QCOPIES = (QTILE / kWave + NW - 1) / NW;        // per wave per head
     constexpr int KCOPIES = KTILE / kWave;                        // = DS
     constexpr int SW = (NCH & (NCH - 1)) == 0 ? NCH - 1 : 0;
@@ -591,13 +593,13 @@ __device__ __forceinline__ void score_task(
     };
 
     // Copy the head's query tile (rows t0 .. t0 + RB - 1) into buffer buf.  Copy j of this
-    // wave fills units U = (wave*QCOPIES + j)*64 + lane: row t = U / NCH, the chunk
+    // wave fills units U = (wave + NW*j)*64 + lane: row t = U / NCH, the chunk
     // stored there is (U % NCH) ^ (t & SW).  Rows past T_b are clamped (their lse2 is
     // +inf, so they weigh exactly 0); the pad chunk past d (HALF) reads chunk 0
     // instead, harmless because the matching key chunk is zero.  The per-lane byte
     // offsets are fixed; a head only moves the base.  The wave's keys likewise (keys past
     // S_b are clamped and never written).
-    uint32_t qoff[QCOPIES], koff[KCOPIES];
+    uint32_t qoff[QCOPIES], koff[KLDS ? KCOPIES : 1];
 #pragma unroll
     for (int j = 0; j < QCOPIES; ++j) {
         const int U = (wave + NW * j) * kWave + lane;
@@ -605,12 +607,16 @@ __device__ __forceinline__ void score_task(
         const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
         qoff[j] = (uint32_t)(t * H * d + e) * 2u;
     }
+    if constexpr (KLDS) {
 #pragma unroll
-    for (int j = 0; j < KCOPIES; ++j) {
-        const int U = j * kWave + lane;
-        const int kc = U / NCH, ch = (U % NCH) ^ (kc & SW);
-        const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
-        koff[j] = (uint32_t)(min(wkey0 + kc, S - 1) * Hkv * d + e) * 2u;
+        for (int j = 0; j < KCOPIES; ++j) {
+            const int U = j * kWave + lane;
+            const int kc = U / NCH, ch = (U % NCH) ^ (kc & SW);
+            const int e = (HALF && ch == NCH - 1) ? 0 : ch * 8;
+            koff[j] = (uint32_t)(min(wkey0 + kc, S - 1) * Hkv * d + e) * 2u;
+        }
+    } else {
+        koff[0] = (uint32_t)(min(wkey0 + lo, S - 1) * Hkv * d) * 2u;
     }
     const char* qrows = reinterpret_cast<const char*>(q + ((size_t)qb + t0) * H * d);
     const char* ksample = reinterpret_cast<const char*>(k + (size_t)kb0 * Hkv * d);
@@ -632,8 +638,8 @@ __device__ __forceinline__ void score_task(
     // Byte offset of fragment (row lo of a 32-row block, chunk hi) for k-step 0; k-step kk
     // reads (frag ^ kk*32) with SW, (frag + kk*32) without.
     const uint32_t frag = (uint32_t)(lo * NCH + (hi ^ (lo & SW))) * 16u;
-    u32x4 kf[DS];
-    auto read_k = [&]() {
+    u32x4 k0[DS], k1[KLDS ? 1 : DS];
+    auto read_k = [&](u32x4 (&kf)[DS]) {
 #pragma unroll
         for (int kk = 0; kk < DS; ++kk) {
             const uint32_t fo = SW ? (frag ^ (uint32_t)(kk * 32)) : frag + kk * 32;
@@ -641,9 +647,18 @@ __device__ __forceinline__ void score_task(
             const u32x4 zero = {0u, 0u, 0u, 0u};
             kf[kk] = (HALF && kk == DS - 1 && hi) ? zero : v;
         }
+#pragma unroll
+        for (int kk = 0; kk < DS; ++kk) settle(kf[kk]);
+    };
+    auto load_k = [&](u32x4 (&kf)[DS]) {
+        const char* base = ksample + (size_t)kv * d * 2 + koff[0];
+#pragma unroll
+        for (int kk = 0; kk < DS; ++kk)
+            kf[kk] = frag16<DS, HALF>(reinterpret_cast<const uint16_t*>(base), kk, hi);
     };
 
-    copy_k();
+    if constexpr (KLDS) copy_k();
+    else load_k(k0);
     copy_q(0);
     const int nsb = min(NSB, (T - t0 + 31) >> 5);
     for (int i = tid; i < H * RB; i += kWave * NW) {
@@ -661,15 +676,18 @@ __device__ __forceinline__ void score_task(
 #pragma unroll
         for (int r = 0; r < 16; ++r) abar[sb][r] = 0.f;
     wait_vmem();
-    read_k();
+    if constexpr (KLDS) {
+        read_k(k0);
+    } else {
 #pragma unroll
-    for (int kk = 0; kk < DS; ++kk) settle(kf[kk]);
+        for (int kk = 0; kk < DS; ++kk) settle(k0[kk]);
+    }
     __syncthreads();
 
-    for (int h = 0; h < H; ++h) {
-        // Start the copies of head h+1, then the MFMA logits of the wave's 32 keys x RB
-        // rows, p = 2^(x - lse2) and the head sum; then wait for the copies, take the next
-        // key fragments and synchronise.
+    // One head: start the copies (or loads) of head h+1, then the MFMA logits of the wave's
+    // 32 keys (kf) x RB rows, p = 2^(x - lse2) and the head sum; then wait for the copies,
+    // take the next key fragments (kn) and synchronise.
+    auto step = [&](int h, const u32x4 (&kf)[DS], u32x4 (&kn)[DS]) {
         const int buf = h & 1;
         const bool more = h + 1 < H;
         const float* l2h = l2t + head * RB + lo;
@@ -677,8 +695,16 @@ __device__ __forceinline__ void score_task(
         advance();
         // Grouped-query heads share their keys.
         const bool nk = more && (group == 1 || kv != kv_now);
+        // Nothing of this wave is in flight here except compiler reloads; waiting for them
+        // now keeps the compiler from waiting inside the head, where that wait would also
+        // cover the loads issued next.
+        if constexpr (!KLDS) wait_vmem();
         if (more) copy_q(buf ^ 1);
-        if (nk) copy_k();
+        if constexpr (KLDS) {
+            if (nk) copy_k();
+        } else {
+            load_k(kn);                          // past the last head: the first one again
+        }
         if (wactive) {
             const char* qtile = reinterpret_cast<const char*>(qt) + buf * QTILE * 16;
             auto chain = [&](int sp) {
@@ -721,12 +747,18 @@ __device__ __forceinline__ void score_task(
             }
         }
         wait_vmem();
-        if (nk) {
-            read_k();
-#pragma unroll
-            for (int kk = 0; kk < DS; ++kk) settle(kf[kk]);
-        }
+        if constexpr (KLDS)
+            if (nk) read_k(kn);
         __syncthreads();
+    };
+    if constexpr (KLDS) {
+        for (int h = 0; h < H; ++h) step(h, k0, k0);
+    } else {
+        for (int h = 0; h < H; h += 2) {
+            step(h, k0, k1);
+            if (h + 1 >= H) break;
+            step(h + 1, k1, k0);
+        }
     }
 
     // Row reduction of Eq. text_scoring (visual keys: max over rows, registers: mean):
@@ -773,23 +805,28 @@ __device__ __forceinline__ void score_task(
 // With fin.done, the last workgroup of each sample forms its scores from the row blocks'
 // partials (text_rows_combine's arithmetic) and, with fin.select, applies the threshold
 // and the compaction (select_kernel's arithmetic).
-// WIDE: eight waves and 128-row blocks that are all full, else four waves and 64-row blocks
-// (score_form).
-template <int DS, bool HALF, bool WIDE>
-__global__ __launch_bounds__((WIDE ? 8 : 4) * kWave, 2) void text_score_kernel(
+// FORM: the workgroup's shape (score_form).  Waves per SIMD that the registers are held to:
+// the tall form needs three at d <= 80 (d = 80 otherwise takes 169 registers: 155 against 143
+// us for 32 samples of 2880 keys x 128 rows), and exactly two from d = 88 (three, at d = 96,
+// 330 against 302 us: the loads are then issued late).
+template <int DS, bool HALF, int FORM>
+__global__ __launch_bounds__(kScoreForms[FORM].waves* kWave)
+    __attribute__((amdgpu_waves_per_eu(FORM == kScoreTall && DS <= 5 ? 3 : 2,
+                                       FORM == kScoreTall && DS >= 6 ? 2 : 8)))
+void text_score_kernel(
     Prob p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const float* __restrict__ lse, int lse_natural, float* __restrict__ scores,
     float* __restrict__ part, Finish fin)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-    constexpr int NW = WIDE ? 8 : 4, NSB = WIDE ? 4 : 2;
-    constexpr int KPW = kTxtKeysPerWave * NW, RB = 32 * NSB, NT = NW * kWave;
+    constexpr int NW = kScoreForms[FORM].waves, RB = kScoreForms[FORM].rows, NSB = RB / 32;
+    constexpr int KPW = kTxtKeysPerWave * NW, NT = NW * kWave;
     const int nchunk = (p.R + p.max_cands + KPW - 1) / KPW;
     const int nrb = (p.max_rows + RB - 1) / RB;
     int b, c, rb;
     if (p.k_off || p.q_off) {
         // The decoded task passes through the start of query buffer 1 (after the first
-        // 128 x d tile), which is first written (head 1's copy) after the barrier that
+        // RB x d tile), which is first written (head 1's copy) after the barrier that
         // ends the task's prologue.
         int* sh = reinterpret_cast<int*>(smem_raw + (size_t)RB * 2 * DS * 16);
         if (threadIdx.x < kWave) ragged_score_task(p, (int)blockIdx.x, KPW, RB, sh);
@@ -811,8 +848,8 @@ __global__ __launch_bounds__((WIDE ? 8 : 4) * kWave, 2) void text_score_kernel(
     // XCD's L2.  A start per key chunk instead fetched 1062 MB per launch at the
     // LLaVA-NeXT shape and 3586 MB on the ragged Qwen3-VL batch; per XCD, 807 and 2654 MB,
     // ~1 % faster.
-    score_task<DS, HALF, NW, NSB, WIDE>(p, q, k, lse, lse_natural, scores, part, b, c, rb,
-                                      (int)blockIdx.x, smem_raw, fin.done != nullptr);
+    score_task<DS, HALF, NW, NSB, kScoreForms[FORM].keys_lds>(
+        p, q, k, lse, lse_natural, scores, part, b, c, rb, (int)blockIdx.x, smem_raw, fin.done != nullptr);
     if (!fin.done) return;
     const int S = keys_of(p, b), T = rows_of(p, b);
     const int nrb_b = (T + RB - 1) / RB;
@@ -988,37 +1025,48 @@ __global__ __launch_bounds__(256) void text_colsum_reduce_kernel(Prob p, const f
     scores[k_begin(p, b) + s] = T > 0 ? acc * (1.f / ((float)p.H * (float)T)) : 0.f;
 }
 
-template <int DS, bool HALF, bool WIDE>
+template <int DS, bool HALF, int FORM>
 static hipError_t score_launch(const Prob& p, const void* q, const void* k, const float* lse,
                                int lse_natural, float* scores, float* part, const Finish& fin,
                                bool leave_blocks, hipStream_t s) {
-    constexpr int NW = WIDE ? 8 : 4, RB = WIDE ? 128 : 64, KPW = kTxtKeysPerWave * NW;
-    size_t smem = score_smem(ScoreForm{NW, RB}, p.H, DS * 16);
+    constexpr ScoreForm f = kScoreForms[FORM];
+    constexpr int RB = f.rows, KPW = kTxtKeysPerWave * f.waves;
+    size_t smem = score_smem(f, p.H, DS * 16);
     if (fin.select) smem = std::max(smem, 128 + select_lds_bytes(p.R, p.max_cands));
     // The tiles need more than the default 64 KB of dynamic LDS: raise the limit (once per
     // device).
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t attr = allow_lds(
-        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, WIDE>), (int)kScoreSmemMax,
+        reinterpret_cast<const void*>(&text_score_kernel<DS, HALF, FORM>), (int)kScoreSmemMax,
         lds_set);
     if (attr != hipSuccess) return attr;
     const int nrb = (p.max_rows + RB - 1) / RB;
     dim3 grid((p.R + p.max_cands + KPW - 1) / KPW * nrb * p.B);
-    const hipError_t e = launch(text_score_kernel<DS, HALF, WIDE>, grid, dim3(NW * kWave), smem, s,
-                                p, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                                lse, lse_natural, scores, nrb > 1 ? part : nullptr, fin);
+    const hipError_t e = launch(text_score_kernel<DS, HALF, FORM>, grid, dim3(f.waves * kWave),
+                                smem, s, p, static_cast<const uint16_t*>(q),
+                                static_cast<const uint16_t*>(k), lse, lse_natural, scores,
+                                nrb > 1 ? part : nullptr, fin);
     if (e != hipSuccess || nrb == 1 || fin.done || leave_blocks) return e;
     dim3 cgrid((p.R + p.max_cands + 255) / 256, p.B);
     return launch(text_rows_combine_kernel, cgrid, dim3(256), 0, s, p, RB, part, scores);
 }
 
+// (score_form takes no wide form up to d = 64 and no tall one from d = 120.)
 template <int DS, bool HALF>
 static hipError_t score_ds(const Prob& p, const void* q, const void* k, const float* lse,
                            int lse_natural, float* scores, float* part, const Finish& fin,
                            bool leave_blocks, hipStream_t s) {
-    if (score_form(p).waves == 8)
-        return score_launch<DS, HALF, true>(p, q, k, lse, lse_natural, scores, part, fin, leave_blocks, s);
-    return score_launch<DS, HALF, false>(p, q, k, lse, lse_natural, scores, part, fin, leave_blocks, s);
+    const int form = score_form(p);
+    if constexpr (DS >= 5)
+        if (form == kScoreWide)
+            return score_launch<DS, HALF, kScoreWide>(p, q, k, lse, lse_natural, scores, part, fin,
+                                                      leave_blocks, s);
+    if constexpr (DS <= 7)
+        if (form == kScoreTall)
+            return score_launch<DS, HALF, kScoreTall>(p, q, k, lse, lse_natural, scores, part, fin,
+                                                      leave_blocks, s);
+    return score_launch<DS, HALF, kScoreNarrow>(p, q, k, lse, lse_natural, scores, part, fin,
+                                                leave_blocks, s);
 }
 
 // d = 16*DS (HALF = false) or 16*DS - 8 (HALF = true), d <= 128.

@@ -78,7 +78,7 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         const int d16 = (d + 15) / 16 * 16;
         if (2 * (size_t)kTxtRows * d16 * 2 + (size_t)H * kTxtRows * 4 > kScoreSmemMax)
             return OCCAM_ERR_UNSUPPORTED;
-        const ScoreForm form = score_form(P.p);
+        const ScoreForm form = kScoreForms[score_form(P.p)];
         const size_t nrb = (max_rows + kTxtRows - 1) / kTxtRows;
         // The statistics pass of a small batch splits every task's keys into ranges, each
         // with its own normaliser table (the scoring pass merges them); not for mutual scoring.
@@ -197,7 +197,7 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
         // keeps two workgroups there), selects.  The counters
         // are cleared by the statistics kernel, so not with a caller normaliser.
         const bool counters = !row_lse && !P.p.mean_rows;
-        const ScoreForm form = score_form(P.p);
+        const ScoreForm form = kScoreForms[score_form(P.p)];
         const bool combine = P.p.max_rows > form.rows;
         const size_t need = 128 + select_lds_bytes(P.p.R, P.p.max_cands);
         const size_t room = score_smem(form, P.p.H, (P.p.d + 15) / 16 * 16);
@@ -232,7 +232,7 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
         if (P.p.mean_rows) return hip_ok(launch_text_colsum(P.p, q, k, lse, natural, part, scores, s));
         // No counters with a caller normaliser: the select that must follow a prune's scoring
         // combines the row blocks.
-        const bool leave = blocks && !fin.done && P.p.max_rows > score_form(P.p).rows;
+        const bool leave = blocks && !fin.done && P.p.max_rows > kScoreForms[score_form(P.p)].rows;
         if (leave) *blocks = part;
         return hip_ok(launch_text_score(P.p, q, k, lse, natural, scores, part, fin, leave, s));
     }
@@ -305,7 +305,7 @@ occam_status run_prune(const Plan& P, const void* q, const void* k, const float*
                         &blocks)) != OCCAM_OK)
         return st;
     if (!selected) {
-        st = hip_ok(launch_select(P.p, sc, blocks, score_form(P.p).rows, nullptr, 1, lambda, reduce,
+        st = hip_ok(launch_select(P.p, sc, blocks, kScoreForms[score_form(P.p)].rows, nullptr, 1, lambda, reduce,
                                   tu, slot, kept_count, stream));
         if (st != OCCAM_OK) return st;
     }

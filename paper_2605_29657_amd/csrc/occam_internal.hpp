@@ -280,38 +280,60 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
     return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
 }
 
-// Forms of the text-row scoring kernel: waves per workgroup (32 keys each) and anchor rows
-// per workgroup.  LDS: two query tiles (rows x d bf16), the waves' keys and the [H][rows]
-// float normaliser table; at most kScoreSmemMax.
+// Forms of the text-row scoring kernel: waves per workgroup (32 keys each), anchor rows per
+// workgroup, and whether the keys reach LDS before the registers.  LDS: two query tiles (rows
+// x d bf16), the waves' keys and the [H][rows] float normaliser table; at most kScoreSmemMax.
 constexpr size_t kScoreSmemMax = 160 * 1024;
 struct ScoreForm {
     int waves, rows;
+    bool keys_lds;
 };
+constexpr int kScoreNarrow = 0, kScoreWide = 1, kScoreTall = 2;
+constexpr ScoreForm kScoreForms[] = {{4, 64, true}, {8, 128, true}, {4, 128, false}};
 inline size_t score_smem(const ScoreForm& f, int H, int d16) {
-    return (2 * (size_t)f.rows + (size_t)f.waves * kTxtKeysPerWave) * d16 * 2 +
+    return (2 * (size_t)f.rows + (f.keys_lds ? (size_t)f.waves * kTxtKeysPerWave : 0)) * d16 * 2 +
            (size_t)H * f.rows * 4;
 }
-// The wide form shares a query tile among twice as many keys and holds twice the rows, so it
-// reads both operands fewer times; it wants whole row blocks and a workgroup for every CU
-// (its LDS leaves room for one).  Video batch (8 x 16384 keys x 256 rows, 1040 wide
-// workgroups): 465 us against 549 us for the narrow form and 522 us for the one before
-// (four waves, 128 rows, keys straight into registers); LLaVA-NeXT (384): 219, 221 and 220.
-// Elsewhere the narrow form's finer tasks win: ragged grouped-query batch (64 samples of
-// 256-4096 keys and 16-512 rows) 427 us against 449 and 470; 32 chained samples of 64-1100
-// keys x 128 rows 70 against 93 and 80; one image (2880 keys x 128 rows) 47, 79 and 63.
-// With key offsets the tasks are counted by the bound max_cands, which a batch of mixed
-// lengths fills about half, so the line lies higher.  Whole call, samples of 64-1100 keys x
-// 128 rows with the caller's normaliser, wide / narrow / former: 40 samples (200 tasks by the
-// bound) 103, 82 and 91 us; 52 (260) 106, 86 and 94; 64 (320) 110, 138 and 133.
-inline ScoreForm score_form(const Prob& p) {
-    const ScoreForm wide{8, 128}, narrow{4, 64};
-    const long long kpw = (long long)wide.waves * kTxtKeysPerWave;
-    const long long tasks = (long long)p.B * ((p.R + (long long)p.max_cands + kpw - 1) / kpw) *
-                            (p.max_rows / wide.rows);
-    return !p.q_off && p.rows % wide.rows == 0 && tasks >= (p.k_off ? 300 : 256) &&
-                   score_smem(wide, p.H, (p.d + 15) / 16 * 16) <= kScoreSmemMax
-               ? wide
-               : narrow;
+// The forms of 128 rows read the keys half as often as the narrow one; they want whole row
+// blocks and a task for every CU.  Elsewhere the narrow form's finer tasks win: ragged
+// grouped-query batch (64 samples of 256-4096 keys and 16-512 rows), scoring pass, narrow
+// 427 us, wide 449, tall 470; one image (2880 keys x 128 rows) 47, 79 and 63.
+// d > 112: wide, whose waves share a query tile among 256 keys (one workgroup per CU at 32
+// heads).  Video batch (8 x 16384 keys x 256 rows, 1040 wide tasks) 465 us, narrow 549, tall
+// 522; LLaVA-NeXT (384) 219, 221 and 220.  With key offsets the tasks are counted by the
+// bound max_cands, which a batch of mixed lengths fills about half, so the line lies higher.
+// Whole call, samples of 64-1100 keys x 128 rows with the caller's normaliser, wide / narrow /
+// tall: 40 samples (200 tasks by the bound) 103, 82 and 91 us; 52 (260) 106, 86 and 94; 64
+// (320) 110, 138 and 133.
+// d <= 112: tall.  A head has less matrix work, so what a head step costs beside it weighs
+// more (the keys' way through LDS, fewer waves per SIMD beside the larger tiles).  Whole call,
+// 32 samples of 2880 keys x 128 rows, tall / narrow / wide: d = 40 (8 heads) 65, 73 and 77 us;
+// 64 (16) 114, 121 and 129; 80 (16) 142, 150 and 150; 96 (32) 302, 320 and 310; 112 (32) 347,
+// 379 and 370.  From d = 72 wide is faster where its last round over the CUs is more than half
+// full (d = 96, 32 heads, wide / tall: 13 samples, 156 tasks, 156 and 164 us; 24, 288, 281 and
+// 264; 34, 408, 339 and 360; 42, 504, 378 and 404), and with key offsets above the same line
+// as at d > 112 (64 samples of 256-4096 keys 407 and 422 us).
+// Below a task of 128 x 128 per CU narrow is the faster one from d = 64 (one image: d = 64 46
+// against 49, d = 96 68 against 82), at d = 40 the slower one (4 samples of 4096 keys: 45
+// against 43).
+inline long long score_tasks(const Prob& p, const ScoreForm& f) {
+    const long long kpw = (long long)f.waves * kTxtKeysPerWave;
+    return (long long)p.B * ((p.R + (long long)p.max_cands + kpw - 1) / kpw) *
+           ((p.max_rows + f.rows - 1) / f.rows);
+}
+inline int score_form(const Prob& p) {
+    const int d16 = (p.d + 15) / 16 * 16;
+    constexpr int rows = kScoreForms[kScoreWide].rows;
+    static_assert(rows == kScoreForms[kScoreTall].rows, "row blocks");
+    if (p.q_off || p.rows % rows != 0) return kScoreNarrow;
+    const long long wide = score_tasks(p, kScoreForms[kScoreWide]), last = wide % 256;
+    const bool enough = p.k_off ? wide >= 300 : d16 > 112 ? wide >= 256 : last == 0 || last >= 150;
+    if (d16 > 64 && enough && score_smem(kScoreForms[kScoreWide], p.H, d16) <= kScoreSmemMax)
+        return kScoreWide;
+    if (d16 > 112) return kScoreNarrow;
+    return d16 < 64 || score_tasks(p, kScoreForms[kScoreTall]) >= (p.k_off ? 512 : 256)
+               ? kScoreTall
+               : kScoreNarrow;
 }
 
 // Dynamic LDS of the text-row statistics kernel: a ring of kStatsRing key blocks

@@ -282,7 +282,7 @@ def test_prune_noalloc_validation(L):
                                  FAKE, FAKE, None) == occam.ERR_INVALID_ARG
 
 
-def text_ws(B, H, T, N, R, blocks, max_rows=None, splits=1):
+def text_ws(B, H, T, N, R, blocks, splits=1):
     """Workspace of a multi-row max problem whose scoring leaves `blocks` row-block partials
     per sample (0: it writes the scores itself), its statistics `splits` normaliser tables."""
     up = lambda n: (n + 255) // 256 * 256
@@ -301,3 +301,13 @@ def test_scoring_form_with_key_offsets(L):
         p = occam.Problem(B, 32, 32, 128, 4, rows=128, cands=1100,
                           key_offsets=FAKE if ragged else None, max_cands=1100)
         assert ws_size(p) == text_ws(B, 32, 128, 1100, 4, blocks), (B, ragged)
+
+
+def test_scoring_form_by_head_dim(L):
+    # d <= 112: 128-row blocks (the tall form) from a 128 x 128 task per CU, at d < 64 always.
+    for d, B, N, blocks in ((40, 4, 4096, 1), (40, 32, 100, 1), (64, 32, 1020, 1),
+                            (64, 31, 1020, 2), (112, 32, 1020, 1), (120, 32, 1020, 2)):
+        p = occam.Problem(B, 32, 32, d, 4, rows=128, cands=N)
+        splits = 8 if B == 4 else 2 if B == 31 else 1
+        splits = max(1, min(splits, ((N + 4 + 31) // 32) // 16))
+        assert ws_size(p) == text_ws(B, 32, 128, N, 4, blocks, splits=splits), (d, B, N)

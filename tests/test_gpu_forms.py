@@ -1,6 +1,6 @@
 """GPU parity where a launch rule of the multi-row kernels changes form: the edges of the
-scoring kernel's two forms (64-row blocks of four waves; 128-row blocks of eight), and the
-dealing of the statistics tasks to the XCDs on ragged batches (unit counts with and without
+scoring kernel's forms (64-row blocks of four waves; 128-row blocks of eight, from d = 120, or
+of four waves with the keys in registers, up to d = 112), and the dealing of the statistics tasks to the XCDs on ragged batches (unit counts with and without
 a remainder, below and above the rule's line)."""
 import pytest
 
@@ -21,8 +21,27 @@ def test_narrow_scoring_form(T):
 @pytest.mark.parametrize("d,Hkv,N", [(64, 1, 8189), (40, 2, 8190), (128, 2, 8191)])
 def test_wide_scoring_form(d, Hkv, N):
     # 4 x 33 x 2 or 4 x 32 x 2 wide workgroups (256 or more); the last chunk full, one short
-    # or one key.
+    # or one key.  (d = 40 and 64: the tall form, twice as many workgroups.)
     sb = custom_stage(B=4, R=2, H=2, Hkv=Hkv, d=d, T=[256] * 4, N=[N] * 4, seed=200 + d)
+    run_and_check(sb, 1.0)
+
+
+@pytest.mark.parametrize("d,H,Hkv,T", [(8, 3, 3, 128), (40, 1, 1, 256), (56, 5, 5, 128),
+                                       (64, 4, 2, 256), (72, 4, 4, 128), (80, 6, 3, 128),
+                                       (96, 2, 2, 256), (104, 3, 1, 128), (112, 2, 1, 256)])
+def test_tall_scoring_form(d, H, Hkv, T):
+    # Key counts around a 128-key chunk and a wave's 32, odd and even head counts (the head
+    # loop takes two steps at a time).  From d = 64 the form needs 512 tasks by the bound.
+    bound = 16384 if d >= 64 and T == 256 else 32766 if d >= 64 else 400
+    N = [125, 126, 127, 9, 0, 400]
+    sb = custom_stage(B=6, R=2, H=H, Hkv=Hkv, d=d, T=[T] * 6, N=N, seed=500 + d)
+    run_and_check(sb, 1.0, ragged=True, row_offsets=False, max_cands=bound)
+
+
+@pytest.mark.parametrize("d", [48, 96])
+def test_tall_scoring_form_uniform(d):
+    # 256 tasks: 4 samples x 32 chunks x 2 row blocks; the last chunk ends one key early.
+    sb = custom_stage(B=4, R=2, H=3, Hkv=3, d=d, T=[256] * 4, N=[4093] * 4, seed=550 + d)
     run_and_check(sb, 1.0)
 
 
