@@ -425,21 +425,32 @@ __device__ __forceinline__ void stats_task(
 // contiguous ranges.  A contiguous range holds whole samples, so with ragged samples the XCD
 // with the longest ones finished last while the others idled (mutual scoring of 16 samples of
 // 256-4096 keys, work ~ keys^2: statistics 697 -> 435 us, column sums 730 -> 470 us; ragged
-// grouped-query batch: statistics 493 -> 430 us).  Uniform batches keep the ranges; so do
-// fewer than eight units per XCD, whose remainder would leave XCDs idle.
-__host__ __device__ __forceinline__ bool stats_by_unit(const Prob& p, int ns) {
-    return (p.k_off || p.q_off) && (long long)p.B * p.Hkv * ns >= 8 * kXcds;
+// grouped-query batch: statistics 493 -> 430 us).  The ranges stay (whole calls, units /
+// ranges)
+//  * on uniform batches, and with fewer than eight units per XCD, whose remainder would leave
+//    XCDs idle;
+//  * where a unit is one workgroup (`per`), which shares nothing, and there are samples
+//    enough to even out: 64 samples of 256-4096 keys x 128 rows, 16 heads of 72 204 and 200
+//    us, 32 of 96 406 and 390, 32 of 112 492 and 466, 32 of 128 468 and 459; 20 of 100-2000
+//    keys, 32 of 112 114 and 109; but 16 samples of 500-4096 keys x 200 rows 200 and 229;
+//  * on short samples whose key slices are no whole 128-byte lines, which the heads side by
+//    side on one XCD share: mutual scoring, 16 heads of 72, 32 samples of 31-250 tokens 43 and
+//    40 us (62-500: 77 and 73, 125-1000: 150 and 166; text rows, 32 heads of 128, 8 samples of
+//    37-300 keys x 250 rows: 62 and 64).
+static bool stats_by_unit(const Prob& p, int ns, int per, int rbw) {
+    return (p.k_off || p.q_off) && (long long)p.B * p.Hkv * ns >= 8 * kXcds &&
+           (per > 1 || p.B <= 16 * rbw) && (p.d % 64 == 0 || p.R + p.max_cands >= 384);
 }
 
 // One statistics task per workgroup.  Task = (sample, head, group of RBW row blocks),
 // groups fastest, XCD-aware: the groups of one (sample, head) read the same keys and
 // meet in one L2; the RBW row blocks of a group share one copy of every key block.
-// Workgroup 0 also clears the per-sample counters of the scoring kernel that follows.
+// per > 0: the tasks are dealt by units of that many (stats_by_unit).  Workgroup 0 also clears the per-sample counters of the scoring kernel that follows.
 template <int DS, bool HALF, bool COLSUM, int RG, int RBW>
 __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
     Prob p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float* __restrict__ lse2, const float* __restrict__ lse_in, int lse_natural,
-    float* __restrict__ part, Finish fin)
+    float* __restrict__ part, int per, Finish fin)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     if (blockIdx.x == 0) clear_done(fin, p.B);
@@ -447,16 +458,15 @@ __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
     const int ngrp = (nrb + RBW - 1) / RBW;
     const int ns = COLSUM || p.lse_splits < 1 ? 1 : p.lse_splits;
     int b, h, tblk, split;
-    if (stats_by_unit(p, ns)) {
+    if (per) {
         // Unit = (sample, key head, key range): the row-block groups of the query heads that
-        // read the same keys.  Units are dealt to the XCDs in turn.
-        const int group = p.H / p.Hkv, per = group * ngrp;
+        // read the same keys, `per` workgroups.  Units are dealt to the XCDs in turn.
         const int j = (int)blockIdx.x / kXcds;
         const int unit = j / per * kXcds + (int)blockIdx.x % kXcds, in = j % per;
         if (unit >= p.B * p.Hkv * ns) return;
         split = unit % ns;
         tblk = in % ngrp;
-        h = (unit / ns) % p.Hkv * group + in / ngrp;
+        h = (unit / ns) % p.Hkv * (p.H / p.Hkv) + in / ngrp;
         b = unit / (ns * p.Hkv);
     } else {
         const int task = xcd_remap((int)blockIdx.x, ngrp * p.H * p.B * ns);
@@ -957,13 +967,13 @@ static hipError_t stats_launch_rg(const Prob& p, const void* q, const void* k, f
     const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
     const int ns = COLSUM || p.lse_splits < 1 ? 1 : p.lse_splits;
     const int ngrp = (nrb + RBW - 1) / RBW;
-    const int units = p.B * p.Hkv * ns;
-    dim3 grid(stats_by_unit(p, ns) ? (units + kXcds - 1) / kXcds * kXcds * (p.H / p.Hkv) * ngrp
-                                   : ngrp * p.H * p.B * ns);
+    const int units = p.B * p.Hkv * ns, per = p.H / p.Hkv * ngrp;
+    const bool deal = stats_by_unit(p, ns, per, RBW);
+    dim3 grid(deal ? (units + kXcds - 1) / kXcds * kXcds * per : per * units);
     const hipError_t e = launch(text_stats_kernel<DS, HALF, COLSUM, RG, RBW>, grid,
                                 dim3(kStatsThreads * RBW), smem, s, p,
                                 static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                                lse2, lse_in, lse_natural, part, fin);
+                                lse2, lse_in, lse_natural, part, deal ? per : 0, fin);
     if (e != hipSuccess || ns == 1) return e;
     const long long n = p.lse_stride;
     const long long nblk = (n + 255) / 256;

@@ -59,11 +59,27 @@ def test_wide_scoring_form_with_key_offsets(T):
 @pytest.mark.parametrize("stage", ["txt", "mut"])
 @pytest.mark.parametrize("B,H,Hkv", [(9, 7, 7), (8, 8, 8), (11, 12, 6)])
 def test_statistics_units(stage, B, H, Hkv):
-    # 63 units (contiguous ranges), 64, and 66 with two query heads each.
+    # 63 units, 64, and 66 with two query heads each (at this head dim and length contiguous
+    # ranges).
     N = [(37 * b * b + 5) % 300 for b in range(B)]
     N[3] = 0
     T = [n + 2 for n in N] if stage == "mut" else [(53 * b + 2) % 290 + 2 for b in range(B)]
     sb = custom_stage(B=B, R=2, H=H, Hkv=Hkv, d=72, T=T, N=N, seed=300 + B, stage=stage)
+    run_and_check(sb, 1.0)
+
+
+@pytest.mark.parametrize("stage", ["txt", "mut"])
+@pytest.mark.parametrize("B,H,Hkv,d,T,longest", [
+    (9, 7, 7, 64, 290, 300), (8, 8, 8, 64, 290, 300), (11, 12, 6, 64, 290, 300),   # 63, 64, 66
+    (16, 4, 4, 128, 100, 300), (17, 4, 4, 128, 100, 300),      # one workgroup per unit
+    (17, 8, 4, 64, 100, 300),                                  # two (query heads)
+    (8, 8, 8, 72, 290, 379), (8, 8, 8, 72, 290, 380)])         # 383 and 384 keys
+def test_statistics_units_dealt(stage, B, H, Hkv, d, T, longest):
+    # Both sides of the lines of the dealing rule; an empty sample among them.
+    N = [(37 * b * b + 5) % 300 for b in range(B)]
+    N[3], N[5] = 0, longest
+    rows = [n + 4 for n in N] if stage == "mut" else [(53 * b + 2) % T + 2 for b in range(B)]
+    sb = custom_stage(B=B, R=4, H=H, Hkv=Hkv, d=d, T=rows, N=N, seed=600 + B, stage=stage)
     run_and_check(sb, 1.0)
 
 
