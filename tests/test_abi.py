@@ -297,7 +297,7 @@ def text_ws(B, H, T, N, R, blocks, splits=1):
 def test_scoring_form_with_key_offsets(L):
     # The wide scoring form (128-row blocks) is chosen by the bound on the keys; a ragged batch
     # fills the bound about half, so it needs more of it than a uniform one.
-    for B, ragged, blocks in ((52, True, 2), (64, True, 1), (52, False, 1), (51, False, 2)):
+    for B, ragged, blocks in ((52, True, 2), (64, True, 1), (52, False, 1), (32, False, 1)):
         p = occam.Problem(B, 32, 32, 128, 4, rows=128, cands=1100,
                           key_offsets=FAKE if ragged else None, max_cands=1100)
         assert ws_size(p) == text_ws(B, 32, 128, 1100, 4, blocks), (B, ragged)
@@ -306,8 +306,20 @@ def test_scoring_form_with_key_offsets(L):
 def test_scoring_form_by_head_dim(L):
     # d <= 112: 128-row blocks (the tall form) from a 128 x 128 task per CU, at d < 64 always.
     for d, B, N, blocks in ((40, 4, 4096, 1), (40, 32, 100, 1), (64, 32, 1020, 1),
-                            (64, 31, 1020, 2), (112, 32, 1020, 1), (120, 32, 1020, 2)):
+                            (64, 31, 1020, 2), (112, 32, 1020, 1), (120, 32, 1020, 2),
+                            (120, 32, 1021, 1)):
         p = occam.Problem(B, 32, 32, d, 4, rows=128, cands=N)
         splits = 8 if B == 4 else 2 if B == 31 else 1
         splits = max(1, min(splits, ((N + 4 + 31) // 32) // 16))
         assert ws_size(p) == text_ws(B, 32, 128, N, 4, blocks, splits=splits), (d, B, N)
+
+
+def test_scoring_form_by_rows(L):
+    # Uniform rows need not fill their last 128-row block for the 128-row forms: one idle
+    # 32-row sub-block to six.
+    for d, T, wide in ((128, 96, False), (128, 97, True), (128, 127, True), (64, 100, True),
+                       (64, 160, False), (128, 192, False), (128, 193, True), (128, 300, False),
+                       (64, 321, True), (96, 250, True), (128, 2000, True)):
+        p = occam.Problem(32, 32, 32, d, 4, rows=T, cands=2880)
+        rows = 128 if wide else 64
+        assert ws_size(p) == text_ws(32, 32, T, 2880, 4, (T + rows - 1) // rows), (d, T)

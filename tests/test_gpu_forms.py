@@ -45,6 +45,14 @@ def test_tall_scoring_form_uniform(d):
     run_and_check(sb, 1.0)
 
 
+@pytest.mark.parametrize("d,T", [(128, 97), (128, 127), (128, 225), (120, 330), (64, 100), (72, 255),
+                                 (40, 449)])
+def test_row_blocks_not_quite_full(d, T):
+    # The 128-row forms with rows past T in the last block: 5 x 28 wide tasks or more.
+    sb = custom_stage(B=5, R=2, H=2, Hkv=1, d=d, T=[T] * 5, N=[7000] * 5, seed=700 + T)
+    run_and_check(sb, 1.0)
+
+
 @pytest.mark.parametrize("T", [128, 256])
 def test_wide_scoring_form_with_key_offsets(T):
     # Ragged keys, uniform rows: 330 or 333 wide tasks by the bound, decoded from the offsets
