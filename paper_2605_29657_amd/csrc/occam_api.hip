@@ -192,17 +192,17 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
     Finish fin{};
     if (selected) *selected = 0;
     if (P.text) {
-        // Text rows: the sample's last scoring workgroup combines the row blocks and, when
-        // the copy of the sample's scores fits in the kernel's LDS (or in half a CU's, which
-        // keeps two workgroups there), selects.  The counters
+        // Text rows: the sample's last scoring workgroup combines the row blocks, when they
+        // are few (combine_in_sample), and selects, when the copy of the sample's scores fits
+        // (score_room).  The counters
         // are cleared by the statistics kernel, so not with a caller normaliser.
         const bool counters = !row_lse && !P.p.mean_rows;
         const ScoreForm form = kScoreForms[score_form(P.p)];
-        const bool combine = P.p.max_rows > form.rows;
+        const bool combine = P.p.max_rows > form.rows, here = combine_in_sample(P.p, form);
         const size_t need = 128 + select_lds_bytes(P.p.R, P.p.max_cands);
-        const size_t room = score_smem(form, P.p.H, (P.p.d + 15) / 16 * 16);
-        const bool do_select = sel && need <= (room > kScoreSmemMax / 2 ? room : kScoreSmemMax / 2);
-        if (counters && (do_select || combine)) {
+        const bool do_select = sel && (here || !combine) &&
+                               need <= score_room(form, P.p.H, (P.p.d + 15) / 16 * 16);
+        if (counters && (do_select || (combine && here))) {
             if (sel) fin = *sel;
             fin.done = ws_at<unsigned>(ws, P.off_done);
             fin.select = do_select ? 1 : 0;
@@ -231,8 +231,10 @@ occam_status run_score(const Plan& P, const void* q, const void* k, const float*
         float* part = ws_at<float>(ws, P.off_part);
         if (P.p.mean_rows) return hip_ok(launch_text_colsum(P.p, q, k, lse, natural, part, scores, s));
         // No counters with a caller normaliser: the select that must follow a prune's scoring
-        // combines the row blocks.
-        const bool leave = blocks && !fin.done && P.p.max_rows > kScoreForms[score_form(P.p)].rows;
+        // combines the row blocks, if they are few.
+        const ScoreForm form = kScoreForms[score_form(P.p)];
+        const bool leave = blocks && !fin.done && P.p.max_rows > form.rows &&
+                           combine_in_sample(P.p, form);
         if (leave) *blocks = part;
         return hip_ok(launch_text_score(P.p, q, k, lse, natural, scores, part, fin, leave, s));
     }

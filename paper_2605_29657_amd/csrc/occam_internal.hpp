@@ -343,6 +343,27 @@ inline int score_form(const Prob& p) {
                : kScoreNarrow;
 }
 
+// LDS a scoring workgroup may take for the copy of its sample's scores: what it has, or up to
+// an equal share of the CU among the workgroups that fit there (registers: at most four).  More
+// would cost workgroups per CU: with half a CU's LDS for every copy, 8 samples of 20000 keys x
+// 100 rows (8 heads of 40) took 165 us, 2 of 16384 x 100 (16 of 64) 106; with the select in
+// a launch of its own 123 and 80.
+inline size_t score_room(const ScoreForm& f, int H, int d16) {
+    const size_t smem = score_smem(f, H, d16), per = kScoreSmemMax / smem;
+    const size_t share = kScoreSmemMax / (per < 1 ? 1 : per > 4 ? 4 : per) / 2048 * 2048;
+    return smem > share ? smem : share;
+}
+// Whether one workgroup per sample combines its row blocks (the last scoring workgroup, or the
+// select with a caller normaliser) instead of text_rows_combine, whose launch it saves: up to
+// 8192 partials, which it reads a few thousand at a time.  Whole calls, in the sample's
+// workgroup / launch of its own: one sample of 2000 keys x 128 rows (2 blocks) 67 and 67 us,
+// with the caller's normaliser 50 and 52; 1000 x 160 (3) 66 and 68; 4096 x 128 (2) 70 and 68;
+// 4096 x 500 (8) 91 and 84; 16384 x 2000 (16) 736 and 710, 16 heads of 64 302 and 247, with the
+// caller's normaliser 188 and 147.
+inline bool combine_in_sample(const Prob& p, const ScoreForm& f) {
+    return (p.max_rows + f.rows - 1) / f.rows * ((long long)p.R + p.max_cands) <= 8192;
+}
+
 // Dynamic LDS of the text-row statistics kernel: a ring of kStatsRing key blocks
 // (32 keys x d bf16) per key stream, plus the (max, sum) merge arrays.  Two stages (one
 // block in flight per stream while the other is used) and four workgroups per CU read

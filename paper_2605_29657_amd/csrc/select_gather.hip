@@ -13,8 +13,8 @@
 //              index, ascending, at its position (mbcnt below the lane) in the
 //              sample's slot of the workspace (slot[co_b + i]).  Optionally computes
 //              tau first (fused threshold of occam_prune), and before that the scores from
-//              the row blocks' partials (occam_prune with a caller normaliser: a
-//              combine launch before it cost the chained batch 92.5 against 90.8 us).  The same compaction runs
+//              the row blocks' partials (occam_prune with a caller normaliser and few
+//              partials: combine_in_sample).  The same compaction runs
 //              in the last workgroup of each sample of the Stage II scoring kernel.
 // pack_gather  grid (G, sample): every wave forms its sample's packed offset
 //              (exclusive sum of the counts before it, with shuffles: no

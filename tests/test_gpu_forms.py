@@ -125,6 +125,65 @@ def test_topk_edges(N, values):
         assert np.array_equal(kept[:K].cpu().numpy(), want)
 
 
+def fused_against_unfused(T, N, d, own_lse, seed, H=4, Hkv=2, R=3, ragged=False):
+    """The fused prune's scores, thresholds and survivors against the unfused calls', bit for
+    bit, on samples of N[b] keys and T[b] rows (uniform unless ragged)."""
+    import numpy as np
+    import torch
+    from paper_2605_29657_amd import occam
+    print("case: T=%s N=%s d=%d lse=%s ragged=%s" % (T, N, d, own_lse, ragged), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    i32 = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32,
+                                 device="cuda")
+    B, keys, total = len(N), sum(N) + R * len(N), sum(N)
+    q = torch.randn(sum(T), H, d, generator=gen, device="cuda").bfloat16()
+    k = torch.randn(keys, Hkv, d, generator=gen, device="cuda").bfloat16()
+    lse = 7.0 + torch.rand(sum(T), H, generator=gen, device="cuda") if own_lse else None
+    p = occam.Problem(B, H, Hkv, d, R, rows=T[0], cands=N[0],
+                      q_offsets=i32(T) if ragged else None,
+                      key_offsets=i32([n + R for n in N]) if ragged else None,
+                      max_rows=max(T), max_cands=max(N))
+    ws = occam.workspace(p)
+    first = torch.zeros(keys, device="cuda")
+    occam.score(p, q, k, first, ws, row_lse=lse)
+    f, ratios, o = first.cpu().numpy(), [], 0
+    for n in N:
+        ratios.append(f[o + R:o + R + n] / f[o:o + R].mean())
+        o += R + n
+    lam = float(np.median(np.concatenate(ratios)))
+    got = []
+    for fused in (True, False):
+        s, tau = torch.zeros(keys, device="cuda"), torch.zeros(B, device="cuda")
+        idx = torch.zeros(total, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(B, dtype=torch.int32, device="cuda")
+        off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+        if fused:
+            occam.prune(p, q, k, lam, idx, cnt, off, ws, scores=s, tau=tau, row_lse=lse)
+        else:
+            occam.score(p, q, k, s, ws, row_lse=lse)
+            occam.threshold(p, s, lam, occam.REG_MEAN, tau)
+            occam.select(p, s, tau, idx, cnt, off, ws)
+        got.append([x.cpu().numpy() for x in (s, tau, idx, cnt, off)])
+    assert 0 < got[0][3].sum() < total
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("own_lse", [False, True])
+@pytest.mark.parametrize("T,N,d,ragged", [
+    ([300, 40, 129], [2044, 0, 1633], 64, True),       # 5 blocks: 10235 partials
+    ([160, 2, 65], [2727, 0, 9], 64, True),            # 3 blocks: 8190 partials
+    ([160, 2, 65], [2728, 0, 9], 64, True),            # 8193
+    ([65] * 2, [4093] * 2, 128, False),                # 2 blocks: 8192
+    ([65] * 2, [4094] * 2, 128, False),                # 8194
+    ([256] * 5, [8189] * 5, 128, False),               # two wide blocks
+    ([100] * 2, [9000] * 2, 40, False),                # one block, scores in a launch of their own
+])
+def test_row_blocks_and_select_placement(T, N, d, ragged, own_lse):
+    # Both sides of the lines for where the row blocks are combined and the survivors selected.
+    fused_against_unfused(T, N, d, own_lse, sum(N), ragged=ragged)
+
+
 @pytest.mark.parametrize("T", [64, 65, 128, 300])
 def test_caller_normaliser_blocks_combined_in_the_select(T):
     # With a caller normaliser the fused prune combines the row blocks in its select: the
