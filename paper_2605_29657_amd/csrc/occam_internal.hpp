@@ -295,18 +295,20 @@ inline size_t score_smem(const ScoreForm& f, int H, int d16) {
            (size_t)H * f.rows * 4;
 }
 // The forms of 128 rows read the keys half as often as the narrow one; they want (nearly)
-// whole row blocks, at most one 32-row sub-block past the rows to six, and tasks for most
-// CUs.  Row blocks that are not quite full (whole calls, 128-row form / narrow, 32 heads of 128
+// whole row blocks, at most one 32-row sub-block past the rows, or one to six, and tasks for
+// most CUs.  Row blocks that are not quite full (whole calls, 128-row form / narrow, 32 heads of 128
 // unless said): 32 samples of 2880 keys x 100 rows 347 and 354 us, 8 of 4096 x 330 312 and
-// 338, 1 of 4096 x 2000 255 and 268, 16 heads 152 and 178; past the line 16 of 4096 x 300 559
-// and 558.  Elsewhere the narrow form's finer tasks win: ragged
+// 338, 1 of 4096 x 2000 255 and 268, 40 of 3000 x 80 406 and 440 (d = 96 345 and 385); past
+// the line 16 of 4096 x 190 397 and 375.  Elsewhere the narrow form's finer tasks win: ragged
 // grouped-query batch (64 samples of 256-4096 keys and 16-512 rows), scoring pass, narrow
 // 427 us, wide 449, tall 470; one image (2880 keys x 128 rows) 47, 79 and 63.
 // d > 112: wide, whose waves share a query tile among 256 keys (one workgroup per CU at 32
 // heads).  Video batch (8 x 16384 keys x 256 rows, 1040 wide tasks) 465 us, narrow 549, tall
 // 522; LLaVA-NeXT (384) 219, 221 and 220.  From 128 wide tasks narrow needs a second round of
 // two workgroups per CU (whole calls, wide / narrow: 4 samples of 8000 keys x 128 rows, 128
-// tasks, 159 and 145 us; 2 of 16384, 130, 158 and 181; 20 of 2880, 240, 213 and 242).
+// tasks, 159 and 145 us; 2 of 16384, 130, 158 and 181; 20 of 2880, 240, 213 and 242), and just
+// past 256 the wide form's own second round is nearly empty (4 of 4096 x 512, 272, 258 and 240;
+// with the caller's normaliser 174 and 158).
 // With key offsets the tasks are counted by the bound max_cands, which a batch of mixed lengths fills about half, so the line lies higher.
 // Whole call, samples of 64-1100 keys x 128 rows with the caller's normaliser, wide / narrow /
 // tall: 40 samples (200 tasks by the bound) 103, 82 and 91 us; 52 (260) 106, 86 and 94; 64
@@ -332,9 +334,11 @@ inline int score_form(const Prob& p) {
     constexpr int rows = kScoreForms[kScoreWide].rows;
     static_assert(rows == kScoreForms[kScoreTall].rows, "row blocks");
     const int subs = (p.rows + 31) / 32, idle = (p.rows + rows - 1) / rows * (rows / 32) - subs;
-    if (p.q_off || 6 * idle > subs) return kScoreNarrow;
+    if (p.q_off || (idle > 1 ? 6 * idle > subs : subs < 3)) return kScoreNarrow;
     const long long wide = score_tasks(p, kScoreForms[kScoreWide]), last = wide % 256;
-    const bool enough = p.k_off ? wide >= 300 : d16 > 112 ? wide > 128 : last == 0 || last >= 150;
+    const bool enough = p.k_off ? wide >= 300
+                        : d16 > 112 ? wide > 128 && (wide <= 256 || wide >= 300)
+                                    : last == 0 || last >= 150;
     if (d16 > 64 && enough && score_smem(kScoreForms[kScoreWide], p.H, d16) <= kScoreSmemMax)
         return kScoreWide;
     if (d16 > 112) return kScoreNarrow;

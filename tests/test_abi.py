@@ -297,7 +297,8 @@ def text_ws(B, H, T, N, R, blocks, splits=1):
 def test_scoring_form_with_key_offsets(L):
     # The wide scoring form (128-row blocks) is chosen by the bound on the keys; a ragged batch
     # fills the bound about half, so it needs more of it than a uniform one.
-    for B, ragged, blocks in ((52, True, 2), (64, True, 1), (52, False, 1), (32, False, 1)):
+    for B, ragged, blocks in ((32, True, 2), (52, True, 2), (64, True, 1), (32, False, 1),
+                               (60, False, 1)):
         p = occam.Problem(B, 32, 32, 128, 4, rows=128, cands=1100,
                           key_offsets=FAKE if ragged else None, max_cands=1100)
         assert ws_size(p) == text_ws(B, 32, 128, 1100, 4, blocks), (B, ragged)
@@ -307,7 +308,8 @@ def test_scoring_form_by_head_dim(L):
     # d <= 112: 128-row blocks (the tall form) from a 128 x 128 task per CU, at d < 64 always.
     for d, B, N, blocks in ((40, 4, 4096, 1), (40, 32, 100, 1), (64, 32, 1020, 1),
                             (64, 31, 1020, 2), (112, 32, 1020, 1), (120, 32, 1020, 2),
-                            (120, 32, 1021, 1)):
+                            (120, 32, 1021, 1), (128, 32, 2044, 1), (128, 32, 2045, 2),
+                            (128, 50, 1532, 1)):
         p = occam.Problem(B, 32, 32, d, 4, rows=128, cands=N)
         splits = 8 if B == 4 else 2 if B == 31 else 1
         splits = max(1, min(splits, ((N + 4 + 31) // 32) // 16))
@@ -317,7 +319,7 @@ def test_scoring_form_by_head_dim(L):
 def test_scoring_form_by_rows(L):
     # Uniform rows need not fill their last 128-row block for the 128-row forms: one idle
     # 32-row sub-block to six.
-    for d, T, wide in ((128, 96, False), (128, 97, True), (128, 127, True), (64, 100, True),
+    for d, T, wide in ((128, 64, False), (128, 65, True), (128, 127, True), (64, 100, True),
                        (64, 160, False), (128, 192, False), (128, 193, True), (128, 300, False),
                        (64, 321, True), (96, 250, True), (128, 2000, True)):
         p = occam.Problem(32, 32, 32, d, 4, rows=T, cands=2880)

@@ -45,7 +45,7 @@ def test_tall_scoring_form_uniform(d):
     run_and_check(sb, 1.0)
 
 
-@pytest.mark.parametrize("d,T", [(128, 97), (128, 127), (128, 225), (120, 330), (64, 100), (72, 255),
+@pytest.mark.parametrize("d,T", [(128, 65), (96, 80), (128, 97), (128, 127), (128, 225), (120, 330), (64, 100), (72, 255),
                                  (40, 449)])
 def test_row_blocks_not_quite_full(d, T):
     # The 128-row forms with rows past T in the last block: 5 x 28 wide tasks or more.
