@@ -3,7 +3,8 @@
 // encoder, the register row of a sample takes the max of channel k over the
 // sample's visual rows, and the visual rows' values of channel k become 0.
 //
-// register_redirect  grid (listed channel, sample), one workgroup each: its threads stride
+// register_redirect  grid (listed channel, sample), one workgroup each, the channels of a
+//                    sample on one XCD (some share the lines of its rows): its threads stride
 //                    over the visual rows, eight 2- or 4-byte reads in flight per thread,
 //                    and clear each element behind its read; a wave and an LDS reduction
 //                    give the maximum, which thread 0 writes to the register.  A
@@ -12,8 +13,10 @@
 //                    element.  A maximum of zero is written as +0.
 //                    Bound by the lines touched (each element sits in a row of its own)
 //                    and, with few of them in flight, by latency: one wave per (channel,
-//                    sample) with one read in flight took 57.9 us for ten channels of the
-//                    LLaVA-NeXT activation (32 x 2884 rows of 8 KB), this form 48.5.
+//                    sample) with one read in flight took 55 to 57 us for ten channels of the
+//                    LLaVA-NeXT activation (32 x 2884 rows of 8 KB), this form 46 to 48 (inputs
+//                    the caches do not hold).  With a sample's channels dealt over the XCDs 64
+//                    channels of 32 x 581 rows took 54 us, on one XCD 38.
 #include "occam_internal.hpp"
 
 namespace occam {
@@ -36,7 +39,9 @@ __global__ __launch_bounds__(NT) void register_redirect_kernel(
     int reg_slot)
 {
     __shared__ float red[NT / kWave];
-    const int j = blockIdx.x, b = blockIdx.y;                  // list entry, sample
+    const int n = (int)gridDim.x;                              // list entries
+    const int task = xcd_remap((int)(blockIdx.y * n + blockIdx.x), n * p.B);
+    const int j = task % n, b = task / n;                      // list entry, sample
     const int k = channels[j];
     int repeat = 0;
     for (int i = threadIdx.x; i < j; i += NT) repeat |= channels[i] == k;
@@ -73,10 +78,14 @@ template <bool BF16>
 static hipError_t redirect(const Prob& p, char* h, int width, long long stride,
                            const int* channels, int n_channels, int reg_slot, hipStream_t s) {
     const dim3 grid(n_channels, p.B);
-    // 1024 threads cover a sample of up to 8192 rows in one round of reads; short samples
-    // leave most of them idle.
+    // Threads for about one read per row and round; more of them idle on short samples, fewer
+    // hold too few reads.  64 channels of 32 x 577 rows, 256 / 512 / 1024 threads: 44, 37 and
+    // 38 us; 30 of 32 x 1100 43, 43 and 40; 64 of 64 x 64 10, 10 and 23.
     if (p.max_cands > 1024)
         return launch(register_redirect_kernel<BF16, 1024>, grid, dim3(1024), 0, s, p, h, width,
+                      stride, channels, reg_slot);
+    if (p.max_cands > 512)
+        return launch(register_redirect_kernel<BF16, 512>, grid, dim3(512), 0, s, p, h, width,
                       stride, channels, reg_slot);
     return launch(register_redirect_kernel<BF16, 256>, grid, dim3(256), 0, s, p, h, width, stride,
                   channels, reg_slot);

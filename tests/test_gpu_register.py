@@ -66,5 +66,16 @@ def test_llava_next_shape_ten_channels():
              ragged=False)
 
 
+@pytest.mark.parametrize("N", [[512, 0, 3], [513, 64], [1024, 1024, 1024, 5], [1025, 2, 800],
+                               [8192, 40], [8193, 8191, 17], [20000, 1]])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_workgroup_sizes_and_rounds(N, dtype):
+    # Both sides of the lines for 256, 512 and 1024 threads and of one round of eight reads per
+    # thread; task counts with and without a remainder over the XCDs; neighbouring channels,
+    # which share lines.
+    run_case(N, R=3, width=96, channels=[5, 6, 95, 0, 6, 40, 41], reg_slot=1, dtype=dtype,
+             seed=sum(N), pad=4)
+
+
 def test_no_channels_is_a_no_op():
     run_case([10, 20], R=2, width=64, channels=[], reg_slot=1, dtype="bf16", seed=4)
