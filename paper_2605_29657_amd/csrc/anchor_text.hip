@@ -990,7 +990,8 @@ static hipError_t stats_launch(const Prob& p, const void* q, const void* k, floa
                                const Finish& fin, hipStream_t s) {
     // The column sums keep one row block per workgroup (their partials are per row block).
     if constexpr (!COLSUM)
-        if (stats_row_blocks((p.max_rows + kTxtRows - 1) / kTxtRows, !p.q_off) == 2)
+        if (stats_row_blocks((p.max_rows + kTxtRows - 1) / kTxtRows, !p.q_off,
+                             (long long)p.B * p.H) == 2)
             return stats_launch_rg<DS, HALF, COLSUM, 4, 2>(p, q, k, lse2, lse_in, lse_natural, part,
                                                            fin, s);
     return stats_launch_rg<DS, HALF, COLSUM, 4, 1>(p, q, k, lse2, lse_in, lse_natural, part, fin, s);

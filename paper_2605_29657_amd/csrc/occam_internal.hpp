@@ -374,15 +374,21 @@ inline bool combine_in_sample(const Prob& p, const ScoreForm& f) {
 // the head slices faster than deeper rings at fewer workgroups per CU: the scattered
 // 256-byte slices stream better with fewer requests outstanding per CU.
 constexpr int kStatsRing = 2;
-// Row blocks per statistics workgroup for nrb 128-row blocks per sample (at most).  Two
-// share each key block's copy where both are nearly always there: an even uniform count, or
-// many of them (the last one alone, half idle, weighs little).  With few row blocks of
-// ragged samples the idle half costs more than the shared copies save: on the grouped-query
-// batch of 64 samples with 16-512 rows the pass takes 394 us with one, 443 us with two and
-// 430 us with four; video (256 rows) 317 us with one, 309 us with two; mutual scoring (up to
-// 33 row blocks) 419 us with one, 406 us with two.
-inline int stats_row_blocks(int nrb, bool uniform) {
-    return nrb >= 8 || (uniform && nrb % 2 == 0) ? 2 : 1;
+// Row blocks per statistics workgroup, for nrb 128-row blocks per sample (at most) and `heads`
+// (sample, head) pairs.  Two share each key block's copy where both are there and the halved
+// launch still fills the chip: always for two or four of a uniform batch (which the key ranges
+// fill, but for mutual scoring); an even uniform count, or from 16 blocks any, with 448 or more
+// workgroups; ragged rows from 32.  Otherwise the idle half, or the CUs without a workgroup,
+// cost more than the shared copies save.  Whole calls, one / two: ragged grouped-query batch
+// (64 samples of 16-512 rows) statistics 394 and 443 us; mutual scoring, 16 heads of 72, 8
+// samples of 1028 rows (9 blocks) 97 and 101, 1 of 4100 (33, 272 workgroups) 202 and 216, 4 of
+// 1404 (11) 88 and 92, 16 of 1704 (14) 358 and 352, 8 of 2884 (23) 496 and 487, 32 ragged of
+// 132-2004 325 and 350, 16 of 260-4100 915 and 903; text, 8 samples of 4096 keys x 700 rows
+// (6) 579 and 569.
+inline int stats_row_blocks(int nrb, bool uniform, long long heads) {
+    if (!uniform) return nrb >= 32 ? 2 : 1;
+    if (nrb <= 4) return nrb % 2 == 0 ? 2 : 1;
+    return heads * ((nrb + 1) / 2) >= 448 && (nrb % 2 == 0 || nrb >= 16) ? 2 : 1;
 }
 // Key ranges of the statistics pass: a batch with fewer than kStatsMinWorkgroups
 // (sample, head, row-block group) tasks splits each task's keys into up to kStatsMaxSplits

@@ -325,3 +325,11 @@ def test_scoring_form_by_rows(L):
         p = occam.Problem(32, 32, 32, d, 4, rows=T, cands=2880)
         rows = 128 if wide else 64
         assert ws_size(p) == text_ws(32, 32, T, 2880, 4, (T + rows - 1) // rows), (d, T)
+
+
+def test_statistics_row_blocks(L):
+    # Two row blocks per statistics workgroup halve the tasks; a launch that then falls below
+    # 1024 of them splits its keys into ranges, each with a normaliser table.  Nine row blocks
+    # (1152 tasks) take one per workgroup and so no ranges.
+    p = occam.Problem(8, 16, 16, 64, 4, rows=1028, cands=1024)
+    assert ws_size(p) == text_ws(8, 16, 1028, 1024, 4, 9)

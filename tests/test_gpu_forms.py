@@ -91,6 +91,19 @@ def test_statistics_units_dealt(stage, B, H, Hkv, d, T, longest):
     run_and_check(sb, 1.0)
 
 
+@pytest.mark.parametrize("stage", ["txt", "mut"])
+@pytest.mark.parametrize("B,H,T", [(5, 30, 700), (4, 28, 700), (3, 32, 520), (7, 10, 650),
+                                   (8, 7, 2049), (8, 8, 1150)])
+def test_statistics_row_blocks(stage, B, H, T):
+    # One or two row blocks per workgroup, uniform: even and odd counts of them on both sides of
+    # 448 workgroups (450, 336, 240, 210, 504, 320).
+    N = [T - 2 if stage == "mut" else 90] * B
+    if stage == "mut":
+        H = max(1, H // 4)
+    sb = custom_stage(B=B, R=2, H=H, Hkv=H, d=40, T=[T] * B, N=N, seed=800 + T, stage=stage)
+    run_and_check(sb, 1.0)
+
+
 @pytest.mark.parametrize("H,d", [(12, 64), (20, 64), (16, 80)])
 @pytest.mark.parametrize("B,lo", [(3, 0), (40, 500)])
 def test_contiguous_run_one_row_form(H, d, B, lo):
