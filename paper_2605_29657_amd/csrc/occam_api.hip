@@ -82,7 +82,10 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         const size_t nrb = (max_rows + kTxtRows - 1) / kTxtRows;
         // The statistics pass of a small batch splits every task's keys into ranges, each
         // with its own normaliser table (the scoring pass merges them); not for mutual scoring.
-        const int rbw = stats_row_blocks((int)nrb, !x.q_offsets, (long long)B * H);
+        // More than four row blocks are counted one by one, also where two share a workgroup of
+        // twice the waves: the halved count would add tables (several megabytes, which took
+        // problems over the built-in workspace's limit) without a measured gain.
+        const int rbw = nrb > 4 ? 1 : stats_row_blocks((int)nrb, !x.q_offsets, (long long)B * H);
         P.p.lse_splits = P.p.mean_rows ? 1 : stats_splits((long long)B * H * ((nrb + rbw - 1) / rbw),
                                                            R + (long long)max_cands);
         P.p.lse_stride = rows_cap * H;

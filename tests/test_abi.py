@@ -333,3 +333,24 @@ def test_statistics_row_blocks(L):
     # (1152 tasks) take one per workgroup and so no ranges.
     p = occam.Problem(8, 16, 16, 64, 4, rows=1028, cands=1024)
     assert ws_size(p) == text_ws(8, 16, 1028, 1024, 4, 9)
+
+
+def noalloc_status(L, p):
+    """Status of the allocation-free call without a device: ERR_WORKSPACE if the problem is
+    refused, else the failed look-up of the built-in workspace."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on the fake addresses")
+    return L.occam_prune_noalloc(p.ref, FAKE, FAKE, None, 1.0, 0, None, 0, None, None, None, FAKE,
+                                 FAKE, FAKE, None)
+
+
+@pytest.mark.parametrize("B,H,d,T,N", [(2, 16, 128, 7882, 62992), (1, 32, 128, 7619, 129891),
+                                       (5, 16, 64, 2189, 82076), (10, 16, 72, 716, 101964)])
+def test_noalloc_limit_tall_batches(L, B, H, d, T, N):
+    # Just within 32 MiB with one normaliser table per key range that the row blocks call for
+    # and their partials counted at 128 rows; some candidates more are refused.
+    p = occam.Problem(B, H, H, d, 4 if d != 72 else 1, rows=T, cands=N)
+    assert noalloc_status(L, p) == occam.ERR_HIP
+    p = occam.Problem(B, H, H, d, 4 if d != 72 else 1, rows=T, cands=N * 51 // 50)
+    assert noalloc_status(L, p) == occam.ERR_WORKSPACE
