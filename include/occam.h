@@ -230,10 +230,10 @@ occam_status occam_prune(const occam_problem *problem, const void *q, const void
  * forbid hipMalloc).  It runs exactly the kernels of occam_prune, with the
  * workspace taken from a static device array built into the library: 64 MiB per
  * GPU, held from the library's first use on that GPU until the process ends.
- * A problem that needs more than 32 MiB, its row-block partials counted at 128
- * rows per block, returns OCCAM_ERR_WORKSPACE (use occam_prune with a workspace
- * of its own).  The
- * array's device address is looked up once per device, on the first call whose
+ * A problem that needs more than 32 MiB returns OCCAM_ERR_WORKSPACE (use
+ * occam_prune with a workspace of its own); its row-block partials are counted
+ * at 128 rows per block, and the chunk lists of 12 and 20 heads of 64 with one
+ * anchor row not at all.  The array's device address is looked up once per device, on the first call whose
  * stream belongs to that device (OCCAM_ERR_HIP if the lookup fails).  The call
  * allocates nothing.  Every call on one GPU shares that GPU's array, so calls
  * that overlap on one GPU (different streams, or different host threads)

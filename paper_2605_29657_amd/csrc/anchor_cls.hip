@@ -524,7 +524,7 @@ __global__ __launch_bounds__(kClsThreads) void cls_scores_kernel(
         total += wcnt[w];
     }
     const size_t list = (size_t)b * nchunks + c;
-    if (keep) fin.chunk_slot[list * kpw + base + below] = key - R;
+    if (keep) fin.chunk_slot[(size_t)b * (R + p.max_cands) + s0 + base + below] = key - R;
     if (threadIdx.x == 0) {
         fin.chunk_cnt[list] = total;
         if (total) atomicAdd(fin.count + b, total);

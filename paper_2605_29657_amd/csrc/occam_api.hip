@@ -26,7 +26,7 @@ struct Plan {
     int nchunks;       // key chunks per sample of the one-row path
     size_t off_logits, off_stats, off_lse2, off_part, off_done, off_clist, off_ccnt, off_scores,
         off_tau, off_slot, off_match, total;
-    size_t finer;      // bytes of off_part beyond what 128-row blocks would take
+    size_t beside;     // bytes not counted against the built-in workspace's limit
 };
 
 bool aligned(const void* ptr, size_t a) { return (reinterpret_cast<uintptr_t>(ptr) % a) == 0; }
@@ -103,8 +103,8 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         // Right behind them, what the max form's 64-row blocks take beyond that (either
         // reduction reserves it, so that the two differ by the column sums alone).
         const size_t blocks = (max_rows + form.rows - 1) / form.rows;
-        if (blocks > 1) P.finer = align_up((blocks - (nrb > 1 ? nrb : 0)) * block);
-        off += P.finer;
+        if (blocks > 1) P.beside = align_up((blocks - (nrb > 1 ? nrb : 0)) * block);
+        off += P.beside;
     } else {
         P.kpw = cls_keys_per_wg(H, x.num_kv_heads, d, bf16 ? 2 : 4, B, R + (long long)max_cands);
         const int NC = d / (bf16 ? 8 : 4);
@@ -121,7 +121,12 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         P.off_stats = off; off = align_up(off + (size_t)B * nchunks * H * sizeof(float2));
         if (nchunks <= kMaxChunkLists) {
             // Per-chunk survivor lists and counts of the in-kernel threshold + compaction.
-            P.off_clist = off; off = align_up(off + (size_t)B * nchunks * P.kpw * sizeof(int));
+            P.off_clist = off; off = align_up(off + (size_t)keys_cap * sizeof(int));
+            // 12 and 20 heads have long chunks, and so lists for longer samples than the
+            // LDS-partials kernel's: not counted against the built-in workspace's limit.
+            if (!cls_stream_nc(H, x.num_kv_heads, d, bf16 ? 2 : 4) &&
+                cls_run_rows(H, x.num_kv_heads, d, bf16 ? 2 : 4))
+                P.beside = off - P.off_clist;
             P.off_ccnt = off; off = align_up(off + (size_t)B * nchunks * sizeof(int));
         }
     }
@@ -324,8 +329,8 @@ occam_status run_prune(const Plan& P, const void* q, const void* k, const float*
 // (held until the process ends).  In host code `scratch` names a host-side stand-in, not
 // device memory: only the address that hipGetSymbolAddress returns for the device,
 // looked up once per device and kept in scratch_ptr, is ever handed to a kernel.
-// kScratchLimit bounds what a problem may need beside its finer row blocks' partials (which
-// never exceed the rest).
+// kScratchLimit bounds what a problem may need beside Plan::beside (which never exceeds the
+// rest).
 constexpr size_t kScratchLimit = size_t(32) << 20, kScratchBytes = 2 * kScratchLimit;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -486,7 +491,7 @@ occam_status occam_prune_noalloc(const occam_problem* problem, const void* q, co
     occam_status st = prune_args(problem, q, k, row_lse, lambda, reduce, index_map, n, tensors,
                                  scores, tau, kept_idx, kept_count, kept_offsets, &P, &rows);
     if (st != OCCAM_OK) return st;
-    if (P.total - P.finer > kScratchLimit || P.total > kScratchBytes) return OCCAM_ERR_WORKSPACE;
+    if (P.total - P.beside > kScratchLimit || P.total > kScratchBytes) return OCCAM_ERR_WORKSPACE;
     void* ws = scratch_for(stream);
     if (!ws) return OCCAM_ERR_HIP;
     return run_prune(P, q, k, row_lse, lambda, reduce, index_map, rows, scores, tau, kept_idx,

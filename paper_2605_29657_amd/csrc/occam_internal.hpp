@@ -474,7 +474,7 @@ struct Finish {
     int* slot;             // survivors, slot[co_b + i]
     int* count;            // [B]
     // One-row path instead (chunk_cnt != null): every scoring workgroup thresholds and
-    // compacts its own chunk of kpw keys into chunk_slot[(b * nchunks + c) * kpw + i],
+    // compacts its own chunk of kpw keys into chunk_slot[b * (R + max_cands) + c * kpw + i],
     // writes chunk_cnt[b * nchunks + c] and adds it to count[b] (cleared by the logits
     // kernel); pack_gather places the chunk lists.
     int* chunk_slot;
@@ -606,7 +606,7 @@ hipError_t launch_select(const Prob& p, float* scores, const float* part, int rb
 // Survivors from the per-chunk lists of the one-row scoring kernel (chunk_cnt != null)
 // or from slot[co_b + i] (select); counts per sample in count[B] either way.
 struct ChunkLists {
-    const int* slot;       // [B][nchunks][kpw]
+    const int* slot;       // [B][R + max_cands], chunk c from c * kpw on
     const int* cnt;        // [B][nchunks]
     int nchunks, kpw;
 };

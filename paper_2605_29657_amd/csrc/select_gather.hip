@@ -156,6 +156,7 @@ __global__ __launch_bounds__(kGatherThreads) void pack_gather_kernel(
         if (tid == kGatherThreads - 1) pc[nlist] = run;
         __syncthreads();
     }
+    const int* chunks = nlist ? lists.slot + (size_t)b * (p.R + p.max_cands) : nullptr;
     // Candidate index of the sample's i-th survivor (any i, per thread).
     auto survivor = [&](int i) -> int {
         if (!nlist) return idx[i];
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kGatherThreads) void pack_gather_kernel(
             const int mid = (lo + hi + 1) >> 1;
             if (pc[mid] <= i) lo = mid; else hi = mid - 1;
         }
-        return lists.slot[((size_t)b * nlist + lo) * lists.kpw + (i - pc[lo])];
+        return chunks[(size_t)lo * lists.kpw + (i - pc[lo])];
     };
     // The same for an i that is uniform over the wave: the chunk is the number of list
     // starts at or below i, less one, counted 64 lists at a time with a ballot.
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kGatherThreads) void pack_gather_kernel(
             n += __popcll(__ballot(c < nlist && pc[c] <= i));
         }
         const int c = n - 1;
-        return lists.slot[((size_t)b * nlist + c) * lists.kpw + (i - pc[c])];
+        return chunks[(size_t)c * lists.kpw + (i - pc[c])];
     };
     if (packed_idx) {
         off = packed_offsets[b];

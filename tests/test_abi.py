@@ -354,3 +354,13 @@ def test_noalloc_limit_tall_batches(L, B, H, d, T, N):
     assert noalloc_status(L, p) == occam.ERR_HIP
     p = occam.Problem(B, H, H, d, 4 if d != 72 else 1, rows=T, cands=N * 51 // 50)
     assert noalloc_status(L, p) == occam.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("B,H,R,N", [(16300, 12, 32, 0), (12453, 12, 8, 34), (3381, 12, 1, 157),
+                                     (2375, 20, 32, 115), (3, 20, 32, 122642), (4, 20, 1, 92013)])
+def test_noalloc_limit_one_row(L, B, H, R, N):
+    # 12 and 20 heads of 64, just within 32 MiB with 64 or 51 keys per chunk and no chunk lists
+    # beyond 1024 chunks; many short samples and few long ones.
+    assert noalloc_status(L, occam.Problem(B, H, H, 64, R, rows=1, cands=N)) == occam.ERR_HIP
+    p = occam.Problem(B + B // 2, H, H, 64, R, rows=1, cands=N)
+    assert noalloc_status(L, p) == occam.ERR_WORKSPACE
