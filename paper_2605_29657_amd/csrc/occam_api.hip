@@ -96,15 +96,14 @@ occam_status make_plan(const occam_problem* pr, Plan* pl) {
         if (P.p.mean_rows) {
             // Column sums of mutual scoring, per (sample, 128-row block, head, key).
             off = align_up(off + nrb * H * block);
-        } else if (nrb > 1) {
-            // Row maxima / sums of the max form, per (sample, 128-row block, key).
-            off = align_up(off + nrb * block);
+        } else {
+            // Row maxima / sums of the max form, per (sample, row block, key).  Beside the
+            // limit: what 64-row blocks take beyond 128-row ones.
+            const size_t blocks = (max_rows + form.rows - 1) / form.rows;
+            const size_t part = blocks > 1 ? align_up(blocks * block) : 0;
+            P.beside = part - (nrb > 1 ? align_up(nrb * block) : 0);
+            off += part;
         }
-        // Right behind them, what the max form's 64-row blocks take beyond that (either
-        // reduction reserves it, so that the two differ by the column sums alone).
-        const size_t blocks = (max_rows + form.rows - 1) / form.rows;
-        if (blocks > 1) P.beside = align_up((blocks - (nrb > 1 ? nrb : 0)) * block);
-        off += P.beside;
     } else {
         P.kpw = cls_keys_per_wg(H, x.num_kv_heads, d, bf16 ? 2 : 4, B, R + (long long)max_cands);
         const int NC = d / (bf16 ? 8 : 4);

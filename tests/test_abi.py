@@ -98,10 +98,10 @@ def test_mutual_scoring_is_a_valid_problem(L):
     # Every token an anchor row, mean over rows (Eq. mutual_scoring).
     p = good_problem(rows=580, cands=576, visual_row_reduce=occam.ROWS_MEAN)
     assert ws_size(p) > 0
-    # Partials per (sample, 128-row block[, head], key): the mean form keeps one per head
-    # (column sums, 4 x 5 x 16 x 580 floats here), the max form one per row block.
+    # Partials per (sample, row block[, head], key): the mean form keeps one per 128-row block
+    # and head (column sums, 4 x 5 x 16 x 580 floats here), the max form one per 64-row block.
     extra = ws_size(p) - ws_size(good_problem(rows=580, cands=576))
-    want = 4 * 5 * (16 - 1) * 580 * 4
+    want = 4 * (5 * 16 - 10) * 580 * 4
     assert want - 256 < extra < want + 256
 
 
@@ -286,10 +286,8 @@ def text_ws(B, H, T, N, R, blocks, splits=1):
     """Workspace of a multi-row max problem whose scoring leaves `blocks` row-block partials
     per sample (0: it writes the scores itself), its statistics `splits` normaliser tables."""
     up = lambda n: (n + 255) // 256 * 256
-    block, nrb = B * (R + N) * 4, (T + 127) // 128
-    part = up(nrb * block if nrb > 1 else 0)
-    if blocks > 1:
-        part += up((blocks - (nrb if nrb > 1 else 0)) * block)
+    block = B * (R + N) * 4
+    part = up(blocks * block) if blocks > 1 else 0
     return (up(splits * B * T * H * 4) + part + up(B * 4) + up(block) + up(B * 4) + up(B * N * 4) +
             8192)
 
