@@ -123,3 +123,39 @@ def test_repeated_calls_reuse_the_workspace():
     ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
     for seed, k, N in ((10, 3.0, [700, 300, 1500]), (11, 40.0, [1500, 2]), (12, 0.0, [5])):
         run_case(N, R=4, k_target=k, seed=seed, ws=ws)
+
+
+@pytest.mark.parametrize("N", [4095, 4096, 4097, 16384])
+def test_samples_of_several_chunks(N):
+    # A workgroup takes 4096 ratios: one chunk full, one of a single ratio, four full ones.
+    run_case([N] * 3, R=2, k_target=N / 7.0, seed=N, ragged=False)
+
+
+@pytest.mark.parametrize("ties", [0, 32])
+def test_ragged_samples_of_several_chunks(ties):
+    # Chunks wholly past a short or empty sample; equal ratios on both sides of a chunk's edge.
+    run_case([16384, 0, 17, 4097, 8192, 12289], R=4, k_target=901.5, seed=20 + ties, ties=ties,
+             zeros=30 if ties else 0)
+
+
+def test_candidate_mean_over_several_chunks():
+    # Every workgroup forms the mean over the whole sample.  Constant samples: their mean, and
+    # with it every ratio, is exact in float32 whatever the order of the sum.
+    N, R, level = [9000, 4096, 5], 2, [0.5, 0.25, 2.0]
+    k_off = np.concatenate([[0], np.cumsum(np.asarray(N) + R)]).astype(np.int64)
+    sc = np.full(int(k_off[-1]), 0.125, dtype=np.float32)
+    for b, n in enumerate(N):
+        sc[k_off[b] + R:k_off[b] + R + n] = level[b]
+        sc[k_off[b] + R] += level[b] / 2                    # one ratio above 1 per sample,
+        sc[k_off[b] + R + n - 1] -= level[b] / 2            # one below, the mean kept
+    p = occam.Problem(3, 16, 16, 64, R, max_cands=max(N),
+                      key_offsets=torch.tensor(k_off.astype(np.int32), device="cuda"))
+    ws = occam.workspace(p)
+    for target, count in ((1.0, 3), (4000.0, sum(N) - 3), (5000.0, sum(N))):
+        out = torch.zeros(2, device="cuda")
+        occam.match_lambda(p, torch.from_numpy(sc).cuda(), target, out[0:1], ws,
+                           mean_kept=out[1:2], reduce=occam.REF_CAND_MEAN)
+        lam, mk = out.cpu().numpy()
+        # Levels: 3 ratios of 1.5, all but 3 of at least 1, all; lambda the geometric midpoint.
+        want = {3: np.sqrt(1.5), sum(N) - 3: np.sqrt(0.5), sum(N): 0.25}[count]
+        assert mk == np.float32(count / 3) and abs(lam - want) < 1e-6, (target, lam, mk)

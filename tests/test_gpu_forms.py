@@ -107,6 +107,7 @@ def test_statistics_row_blocks(stage, B, H, T):
 @pytest.mark.parametrize("H,d", [(12, 64), (20, 64), (16, 80)])
 @pytest.mark.parametrize("B,lo", [(3, 0), (40, 500)])
 def test_contiguous_run_one_row_form(H, d, B, lo):
+    # (16 x 80 takes the padded form: the other side of the rule.)
     # Key counts around the wave's run of rows and the workgroup's chunk (16 keys for three
     # samples, 128 for forty), an empty sample among them.
     N = [0, 1, 127, 126, 3][:B] + [lo + 13 * b for b in range(B - 5)]

@@ -298,9 +298,9 @@ def test_lambda_zero_keeps_everything_and_huge_keeps_nothing():
 
 
 def test_uniform_rows_with_ragged_keys():
-    # Ragged key counts, every sample 128 or 256 text rows, passed without row offsets:
-    # the scoring pass's full-row-block form meets the ragged task mapping (and, at 256
-    # rows, the combine over two row blocks).
+    # Ragged key counts, every sample 128 or 256 text rows, passed without row offsets: the
+    # ragged task mapping over uniform rows, and the combine of two and four row blocks (too
+    # few tasks for the forms of 128 rows).
     for T in (128, 256):
         sb = custom_stage(B=4, R=4, H=8, Hkv=8, d=128, T=[T] * 4, N=[700, 30, 0, 260], seed=T)
         run_and_check(sb, 1.0, ragged=True, row_offsets=False)
