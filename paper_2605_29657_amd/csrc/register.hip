@@ -39,9 +39,13 @@ __global__ __launch_bounds__(NT) void register_redirect_kernel(
     int reg_slot)
 {
     __shared__ float red[NT / kWave];
-    const int n = (int)gridDim.x;                              // list entries
-    const int task = xcd_remap((int)(blockIdx.y * n + blockIdx.x), n * p.B);
-    const int j = task % n, b = task / n;                      // list entry, sample
+    int j = blockIdx.x, b = blockIdx.y;                        // list entry, sample
+    const int n = (int)gridDim.x;
+    if (n * p.B >= kXcds * 32) {             // (fewer find a CU of their own, line or not)
+        const int task = xcd_remap(b * n + j, n * p.B);
+        j = task % n;
+        b = task / n;
+    }
     const int k = channels[j];
     int repeat = 0;
     for (int i = threadIdx.x; i < j; i += NT) repeat |= channels[i] == k;
@@ -80,11 +84,12 @@ static hipError_t redirect(const Prob& p, char* h, int width, long long stride,
     const dim3 grid(n_channels, p.B);
     // Threads for about one read per row and round; more of them idle on short samples, fewer
     // hold too few reads.  64 channels of 32 x 577 rows, 256 / 512 / 1024 threads: 44, 37 and
-    // 38 us; 30 of 32 x 1100 43, 43 and 40; 64 of 64 x 64 10, 10 and 23.
+    // 38 us; 10 of 16 x 1024 9.1, 9.3 and 9.3; 30 of 32 x 1100 43, 43 and 40; 64 of 64 x 64
+    // 10, 10 and 23.
     if (p.max_cands > 1024)
         return launch(register_redirect_kernel<BF16, 1024>, grid, dim3(1024), 0, s, p, h, width,
                       stride, channels, reg_slot);
-    if (p.max_cands > 512)
+    if (p.max_cands > 512 && (long long)p.B * n_channels >= 512)
         return launch(register_redirect_kernel<BF16, 512>, grid, dim3(512), 0, s, p, h, width,
                       stride, channels, reg_slot);
     return launch(register_redirect_kernel<BF16, 256>, grid, dim3(256), 0, s, p, h, width, stride,
