@@ -293,12 +293,12 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_kernel(
 // of a head (4 waves x KB rows) are merged in a fixed order at the end.  Bound by HBM (64
 // samples of 256-4096 keys, 16 x 72: 344 MB in 66 us); a batch of 24 samples of 97-1200
 // keys with 12 heads of 64 took 27.4 us through cls_logits_kernel and its LDS table.
-template <bool BF16, int HH, int NCK, int KB>
+template <int HH, int NCK, int KB>
 __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
     Prob p, const void* __restrict__ qv, const void* __restrict__ kv,
     float* __restrict__ logits, float2* __restrict__ stats, int kpw, int nchunks, Finish fin)
 {
-    constexpr int CE = BF16 ? 8 : 4;                 // elements per 16-byte chunk
+    constexpr int CE = 8;                            // bf16 elements per 16-byte chunk
     static_assert(KB * HH <= kWave, "one lane per (row, head)");
     constexpr int ROWC = HH * NCK;                   // 16-byte chunks per key row
     constexpr int NJ = KB * ROWC / kWave;            // loads per lane per step
@@ -324,15 +324,9 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
     for (int j = 0; j < NJ; ++j) {
         const int col = (j * kWave + lane) % ROWC;
         const int h = col / NCK, e0 = (col % NCK) * CE;
-        if constexpr (BF16) {
-            const uint16_t* q16 = static_cast<const uint16_t*>(qv) + ((size_t)qrow * HH + h) * d + e0;
+        const uint16_t* q16 = static_cast<const uint16_t*>(qv) + ((size_t)qrow * HH + h) * d + e0;
 #pragma unroll
-            for (int e = 0; e < CE; ++e) qf[j][e] = __uint_as_float(static_cast<uint32_t>(q16[e]) << 16);
-        } else {
-            const float* q32 = static_cast<const float*>(qv) + ((size_t)qrow * HH + h) * d + e0;
-#pragma unroll
-            for (int e = 0; e < CE; ++e) qf[j][e] = q32[e];
-        }
+        for (int e = 0; e < CE; ++e) qf[j][e] = __uint_as_float(static_cast<uint32_t>(q16[e]) << 16);
     }
 
     const int rr = lane / HH, hh = lane % HH;        // this lane's (row of the run, head)
@@ -352,16 +346,8 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
         }
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            float kf[CE];
-            if constexpr (BF16) {
-                kf[0] = bf16_lo(w[j].x); kf[1] = bf16_hi(w[j].x);
-                kf[2] = bf16_lo(w[j].y); kf[3] = bf16_hi(w[j].y);
-                kf[4] = bf16_lo(w[j].z); kf[5] = bf16_hi(w[j].z);
-                kf[6] = bf16_lo(w[j].w); kf[7] = bf16_hi(w[j].w);
-            } else {
-                kf[0] = __uint_as_float(w[j].x); kf[1] = __uint_as_float(w[j].y);
-                kf[2] = __uint_as_float(w[j].z); kf[3] = __uint_as_float(w[j].w);
-            }
+            const float kf[CE] = {bf16_lo(w[j].x), bf16_hi(w[j].x), bf16_lo(w[j].y), bf16_hi(w[j].y),
+                                  bf16_lo(w[j].z), bf16_hi(w[j].z), bf16_lo(w[j].w), bf16_hi(w[j].w)};
             float acc = 0.f;
 #pragma unroll
             for (int e = 0; e < CE; ++e) acc = fmaf(qf[j][e], kf[e], acc);
@@ -382,10 +368,10 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
         if (mine && k0 + rr < nk) {
             lout[(size_t)(k0 + rr) * HH + hh] = l;
             if (l > m) {
-                z = z * cls_exp<BF16>(m - l) + 1.f;
+                z = z * cls_exp<true>(m - l) + 1.f;
                 m = l;
             } else {
-                z += cls_exp<BF16>(l - m);
+                z += cls_exp<true>(l - m);
             }
         }
     }
@@ -403,7 +389,7 @@ __global__ __launch_bounds__(kClsThreads) void cls_stream_run_kernel(
                 const float mo = red_m[w2][r * HH + h], zo = red_z[w2][r * HH + h];
                 const float mn = fmaxf(mm, mo);
                 if (mn != -INFINITY) {
-                    zz = zz * cls_exp<BF16>(mm - mn) + zo * cls_exp<BF16>(mo - mn);
+                    zz = zz * cls_exp<true>(mm - mn) + zo * cls_exp<true>(mo - mn);
                     mm = mn;
                 }
             }
@@ -577,13 +563,13 @@ hipError_t launch_cls_logits(const Prob& p, int bf16, const void* q, const void*
         const auto run = [&](auto kernel) {
             return launch(kernel, grid, blk, 0, s, p, q, k, logits, stats, kpw, nchunks, fin);
         };
-        if (p.H == 12) return run(cls_stream_run_kernel<true, 12, 8, 4>);
-        if (p.H == 20) return run(cls_stream_run_kernel<true, 20, 8, 2>);
+        if (p.H == 12) return run(cls_stream_run_kernel<12, 8, 4>);
+        if (p.H == 20) return run(cls_stream_run_kernel<20, 8, 2>);
         switch (p.d) {
-        case 40: return run(cls_stream_run_kernel<true, 16, 5, 4>);
-        case 48: return run(cls_stream_run_kernel<true, 16, 6, 4>);
-        case 56: return run(cls_stream_run_kernel<true, 16, 7, 4>);
-        default: return run(cls_stream_run_kernel<true, 16, 9, 4>);
+        case 40: return run(cls_stream_run_kernel<16, 5, 4>);
+        case 48: return run(cls_stream_run_kernel<16, 6, 4>);
+        case 56: return run(cls_stream_run_kernel<16, 7, 4>);
+        default: return run(cls_stream_run_kernel<16, 9, 4>);
         }
     }
     const int nc = cls_stream_nc(p.H, p.Hkv, p.d, bf16 ? 2 : 4);

@@ -15,16 +15,15 @@
 // text_stats  task (sample, head, group of one or two row blocks of 128[, key range]),
 //             XCD-aware; a batch with few such tasks splits their keys into ranges whose tables
 //             text_lse_merge combines.
-//             One key stream consumed by four waves of 32 rows per row block (the
-//             kernel also has a two-stream form of two 64-row waves each), so each
+//             The keys are consumed by four waves of 32 rows per row block, so each
 //             key block is copied once for every row block of the group; the
 //             query rows of the head sit in
 //             registers as MFMA B fragments, and a (reference, sum 2^(x - reference))
 //             pair is kept per row: the reference is the first key block's maximum
 //             and moves only when a block's sum would exceed 2^64, so a logit costs
 //             a multiply-add, an exponential and an add (no running maximum); pairs
-//             are merged across the two lane halves (and
-//             streams) in a fixed order.  Key blocks reach LDS through direct global -> LDS
+//             are merged across the two lane halves
+//             in a fixed order.  Key blocks reach LDS through direct global -> LDS
 //             copies (a 2-stage ring per stream).  Writes the base-2
 //             log-sum-exp lse2[row, head] of x = logit * log2(e).  Its COLSUM
 //             form streams the keys the same way with the normalisers known and
@@ -127,7 +126,7 @@ __device__ __forceinline__ void wait_vmem_le() {
 // fixed-order sum over the partials (text_colsum_reduce).  Both modes stream the keys
 // the same way; the column sums use the MFMA the other way round (rows as the A
 // operand), so that a lane holds 16 rows of one key and sums them in registers.
-template <int DS, bool HALF, bool COLSUM, int RG, int RING, int RBW>
+template <int DS, bool HALF, bool COLSUM, int RING, int RBW>
 __device__ __forceinline__ void stats_task(
     const Prob& p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float* __restrict__ lse2, const float* __restrict__ lse_in, int lse_natural,
@@ -135,46 +134,39 @@ __device__ __forceinline__ void stats_task(
 {
     // Keys: range split of nsplit (32-key blocks [kb_lo, kb_lo + nkb_s) of the sample);
     // the base-2 log-sum-exp over that range goes to table split of lse2.
-    // RBW row blocks (tblk * RBW + rbl, rbl < RBW) of kStatsThreads / 64 waves each; the
-    // waves of a row block form kStreams key streams of RG waves: wave w of row block rbl
-    // owns the RPW = 128 / RG rows [rg*RPW, +RPW) of it (rg = w % RG) and the key stream
-    // ks = w / RG (key blocks kbi = ks mod kStreams).  The RG * RBW waves of a stream (all
-    // row blocks) consume the same key blocks, so each block is copied once per stream,
-    // global -> LDS, into a ring of RING stages per stream: RING - 1 blocks are in
-    // flight while one is used.  RG = 4 (32 rows per wave) needs half the registers of
-    // RG = 2 and runs more waves per SIMD; the launcher uses it for every row count.
+    // RBW row blocks (tblk * RBW + rbl, rbl < RBW) of RG = 4 waves each: wave rg of a row
+    // block owns its 32 rows [32 rg, +32).  All NW waves consume the same key blocks, so each
+    // block is copied once, global -> LDS, into a ring of RING stages: RING - 1 blocks are in
+    // flight while one is used.
     // A row block past T_b computes nothing but still copies its share of the blocks and
     // meets every barrier.
     // A block is 32 keys x NCH 16-byte chunks; chunk c of key j sits in LDS unit
     // j*NCH + (c ^ (j & SW)), SW = NCH - 1 when NCH is a power of two (else 0), so a
     // copy writes whole 256-byte key slices and the MFMA fragment reads of 32
     // consecutive keys spread over the banks.
-    static_assert(RG == 2 || RG == 4, "row groups per stream");
     static_assert(RBW == 1 || !COLSUM, "column sums take one row block per workgroup");
+    constexpr int RG = kStatsThreads / kWave;        // waves of a row block
     constexpr int RPW = kTxtRows / RG;               // rows per wave
     constexpr int NSBW = RPW / 32;                   // 32-row sub-blocks per wave
-    constexpr int kStreams = kStatsThreads / kWave / RG;
-    constexpr int NW = RG * RBW;                     // waves of one key stream
+    constexpr int NW = RG * RBW;                     // waves of the workgroup
     constexpr int NCH = 2 * DS;                      // 16-byte chunks per key row
     constexpr int UNITS = 32 * NCH;                  // 16-byte units per block
     constexpr int COPIES = UNITS / kWave;            // = DS copies of 64 lanes per block
-    constexpr int MINE = (COPIES + NW - 1) / NW;     // most copies a stream member issues
-    constexpr int MINE_MIN = COPIES / NW;            // fewest copies a stream member issues
+    constexpr int MINE = (COPIES + NW - 1) / NW;     // most copies a wave issues
+    constexpr int MINE_MIN = COPIES / NW;            // fewest copies a wave issues
     constexpr int SW = (NCH & (NCH - 1)) == 0 ? NCH - 1 : 0;
-    u32x4* ring = reinterpret_cast<u32x4*>(smem_raw);              // [stream][stage][UNITS]
-    float* red_m = reinterpret_cast<float*>(ring + kStreams * RING * UNITS);
-    float* red_z = red_m + kStreams * RBW * kTxtRows;
+    u32x4* ring = reinterpret_cast<u32x4*>(smem_raw);              // [stage][UNITS]
+    float* red_m = reinterpret_cast<float*>(ring + RING * UNITS);
+    float* red_z = red_m + RBW * kTxtRows;
     const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
     const int T = rows_of(p, b);
     if (tblk * RBW * kTxtRows >= T) return;
     const int S = keys_of(p, b);
     const int lane = threadIdx.x & 63;
-    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
-    const int rbl = wave_all / (kStatsThreads / kWave), wave = wave_all % (kStatsThreads / kWave);
+    const int mi = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);         // wave-uniform
+    const int rbl = mi / RG, rg = mi % RG;
     const int t0 = (tblk * RBW + rbl) * kTxtRows;
     const int hi = lane >> 5, lo = lane & 31;
-    const int rg = wave % RG, ks = wave / RG;
-    const int mi = rbl * RG + rg;                      // member index within the stream
     const int H = p.H, Hkv = p.Hkv, d = p.d;
     const int g = h / (H / Hkv);
     const int tw = t0 + rg * RPW;                      // first row of this wave
@@ -215,13 +207,11 @@ __device__ __forceinline__ void stats_task(
     const int nkb = (S + 31) >> 5;
     const int kb_lo = __builtin_amdgcn_readfirstlane(nkb * split / nsplit);   // wave-uniform
     const int nkb_s = __builtin_amdgcn_readfirstlane(nkb * (split + 1) / nsplit) - kb_lo;
-    const int nmine = (nkb_s - ks + kStreams - 1) / kStreams;   // blocks of this stream
     const char* kbase = reinterpret_cast<const char*>(k + ((size_t)kb0 * Hkv + g) * d);
     const int kstride = Hkv * d;                      // elements per key row
-    u32x4* sring = ring + ks * RING * UNITS;
-    const uint32_t sring_lds = lds_addr(sring);
+    const uint32_t ring_lds = lds_addr(ring);
 
-    // Copy block j of this stream (clamped to the stream's last block) into its stage.
+    // Copy block j of the range (clamped to its last block) into its stage.
     // Copy c of the block fills units 64c .. 64c+63; this wave issues c = mi, mi+NW, ...
     // Lane offsets inside a block are fixed (key kc = u / NCH of the block, chunk
     // (u % NCH) ^ (kc & SW)); only a block running past S_b clamps its keys.  The pad
@@ -235,14 +225,12 @@ __device__ __forceinline__ void stats_task(
         coff[i] = (uint32_t)(kc * kstride + e) * 2u;
     }
     auto issue = [&](int j) {
-        const int jj = min(j, max(nmine - 1, 0));
-        // A stream with no block of its own (nmine == 0) copies the range's (or the
-        // sample's) last block: every copy stays inside the sample's keys, and the stage is
-        // never read.
-        const int klast = nkb_s > 0 ? kb_lo + nkb_s - 1 : nkb - 1;
-        const int kbi = min(kb_lo + ks + jj * kStreams, klast);
+        const int jj = min(j, max(nkb_s - 1, 0));
+        // An empty range copies the sample's last block at most: every copy stays inside the
+        // sample's keys, and the stage is never read.
+        const int kbi = min(kb_lo + jj, nkb - 1);
         const char* bbase = kbase + (size_t)kbi * 32 * kstride * 2;
-        const uint32_t dst = sring_lds + (uint32_t)((jj % RING) * UNITS * 16);
+        const uint32_t dst = ring_lds + (uint32_t)((jj % RING) * UNITS * 16);
         const bool full = kbi * 32 + 32 <= S;
 #pragma unroll
         for (int i = 0; i < MINE; ++i) {
@@ -357,17 +345,14 @@ __device__ __forceinline__ void stats_task(
         return 0.f;
     };
 
-    // Every wave runs the same number of iterations (the most any stream has), so the
-    // barriers match; a stream past its last block only re-issues its last block.
-    const int iters = (nkb_s + kStreams - 1) / kStreams;
-    // COLSUM: the RG waves of a stream leave their column sums of block j in
-    // sums[j & 1][ks][rg][key] (red_m and red_z together); after the next barrier the
+    // COLSUM: the RG waves leave their column sums of block j in
+    // sums[j & 1][rg][key] (red_m and red_z together); after the next barrier the
     // rg = 0 wave adds them in order of rg and stores the workgroup's partial.
     float* sums = red_m;
     float* prow = part + (((size_t)b * nrb + tblk) * H + h) * (size_t)(p.R + p.max_cands);
     auto store_sums = [&](int j) {
-        const float* sp = sums + ((j & 1) * kStreams + ks) * (RG * 32);
-        const int key = (ks + j * kStreams) * 32 + lane;
+        const float* sp = sums + (j & 1) * (RG * 32);
+        const int key = j * 32 + lane;
         if (lane < 32 && key < S) {
             float v = sp[lane];
 #pragma unroll
@@ -377,47 +362,41 @@ __device__ __forceinline__ void stats_task(
     };
 #pragma unroll
     for (int j = 0; j < RING - 1; ++j) issue(j);
-    for (int i = 0; i < iters; ++i) {
+    for (int i = 0; i < nkb_s; ++i) {
         // Own copies of block i have landed once at most RING-2 later blocks remain
-        // (counted with the fewest copies a member issues: a stronger wait for the others).
+        // (counted with the fewest copies a wave issues: a stronger wait for the others).
         wait_vmem_le<(RING - 2) * MINE_MIN>();
         __syncthreads();                 // partner's copies landed; stage (i-1) is free
         issue(i + RING - 1);
-        if (COLSUM && rg == 0 && i >= 1 && i - 1 < nmine) store_sums(i - 1);
-        if (i < nmine) {
-            float cs = 0.f;
-            if (nsb > 0) cs = block(kb_lo + ks + i * kStreams, sring + (i % RING) * UNITS, i == 0);
-            if (COLSUM && hi == 0) sums[((i & 1) * kStreams + ks) * (RG * 32) + rg * 32 + lo] = cs;
-        }
+        if (COLSUM && rg == 0 && i >= 1) store_sums(i - 1);
+        float cs = 0.f;
+        if (nsb > 0) cs = block(kb_lo + i, ring + (i % RING) * UNITS, i == 0);
+        if (COLSUM && hi == 0) sums[(i & 1) * (RG * 32) + rg * 32 + lo] = cs;
     }
     wait_vmem_le<0>();
     if (COLSUM) {
         __syncthreads();
-        if (rg == 0 && iters >= 1 && iters - 1 < nmine) store_sums(iters - 1);
+        if (rg == 0 && nkb_s >= 1) store_sums(nkb_s - 1);
         return;
     }
 
-    // Merge the two lane halves (same rows, different keys), then the key streams.
+    // Merge the two lane halves (same rows, different keys).
 #pragma unroll
     for (int sb = 0; sb < NSBW; ++sb) {
         const float mo = __shfl_xor(m[sb], 32);
         const float zo = __shfl_xor(z[sb], 32);
         merge_pair(m[sb], z[sb], mo, zo);
         if (hi == 0) {
-            red_m[(rbl * kStreams + ks) * kTxtRows + rg * RPW + sb * 32 + lo] = m[sb];
-            red_z[(rbl * kStreams + ks) * kTxtRows + rg * RPW + sb * 32 + lo] = z[sb];
+            red_m[rbl * kTxtRows + rg * RPW + sb * 32 + lo] = m[sb];
+            red_z[rbl * kTxtRows + rg * RPW + sb * 32 + lo] = z[sb];
         }
     }
     __syncthreads();
     if (threadIdx.x < RBW * kTxtRows) {
         const int rr = threadIdx.x / kTxtRows, i = threadIdx.x % kTxtRows;
-        const float* rm = red_m + rr * kStreams * kTxtRows;
-        const float* rz = red_z + rr * kStreams * kTxtRows;
-        float mm = rm[i], zz = rz[i];
-        for (int w = 1; w < kStreams; ++w) merge_pair(mm, zz, rm[w * kTxtRows + i], rz[w * kTxtRows + i]);
         const int t = (tblk * RBW + rr) * kTxtRows + i;
         if (t < T) lse2[(size_t)split * p.lse_stride + (size_t)(qb + t) * H + h] =
-            mm + __builtin_amdgcn_logf(zz);
+            red_m[threadIdx.x] + __builtin_amdgcn_logf(red_z[threadIdx.x]);
     }
 }
 
@@ -446,7 +425,7 @@ static bool stats_by_unit(const Prob& p, int ns, int per, int rbw) {
 // groups fastest, XCD-aware: the groups of one (sample, head) read the same keys and
 // meet in one L2; the RBW row blocks of a group share one copy of every key block.
 // per > 0: the tasks are dealt by units of that many (stats_by_unit).  Workgroup 0 also clears the per-sample counters of the scoring kernel that follows.
-template <int DS, bool HALF, bool COLSUM, int RG, int RBW>
+template <int DS, bool HALF, bool COLSUM, int RBW>
 __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
     Prob p, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float* __restrict__ lse2, const float* __restrict__ lse_in, int lse_natural,
@@ -481,8 +460,8 @@ __global__ __launch_bounds__(kStatsThreads * RBW, 1) void text_stats_kernel(
     h = __builtin_amdgcn_readfirstlane(h);
     tblk = __builtin_amdgcn_readfirstlane(tblk);
     split = __builtin_amdgcn_readfirstlane(split);
-    stats_task<DS, HALF, COLSUM, RG, kStatsRing, RBW>(p, q, k, lse2, lse_in, lse_natural, part,
-                                                      b, h, tblk, split, ns, smem_raw);
+    stats_task<DS, HALF, COLSUM, kStatsRing, RBW>(p, q, k, lse2, lse_in, lse_natural, part, b,
+                                                  h, tblk, split, ns, smem_raw);
 }
 
 // Ragged launches: workgroup id -> the id-th non-empty (sample, key chunk, row block)
@@ -965,14 +944,14 @@ __global__ __launch_bounds__(256) void text_lse_merge_kernel(Prob p, float* __re
     }
 }
 
-template <int DS, bool HALF, bool COLSUM, int RG, int RBW>
-static hipError_t stats_launch_rg(const Prob& p, const void* q, const void* k, float* lse2,
+template <int DS, bool HALF, bool COLSUM, int RBW>
+static hipError_t stats_launch_rbw(const Prob& p, const void* q, const void* k, float* lse2,
                                   const float* lse_in, int lse_natural, float* part,
                                   const Finish& fin, hipStream_t s) {
-    const size_t smem = text_stats_smem(DS * 16, RG, RBW);
+    const size_t smem = text_stats_smem(DS * 16, RBW);
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t attr = allow_lds(
-        reinterpret_cast<const void*>(&text_stats_kernel<DS, HALF, COLSUM, RG, RBW>),
+        reinterpret_cast<const void*>(&text_stats_kernel<DS, HALF, COLSUM, RBW>),
         (int)kScoreSmemMax, lds_set);
     if (attr != hipSuccess) return attr;
     const int nrb = (p.max_rows + kTxtRows - 1) / kTxtRows;
@@ -981,7 +960,7 @@ static hipError_t stats_launch_rg(const Prob& p, const void* q, const void* k, f
     const int units = p.B * p.Hkv * ns, per = p.H / p.Hkv * ngrp;
     const bool deal = stats_by_unit(p, ns, per, RBW);
     dim3 grid(deal ? (units + kXcds - 1) / kXcds * kXcds * per : per * units);
-    const hipError_t e = launch(text_stats_kernel<DS, HALF, COLSUM, RG, RBW>, grid,
+    const hipError_t e = launch(text_stats_kernel<DS, HALF, COLSUM, RBW>, grid,
                                 dim3(kStatsThreads * RBW), smem, s, p,
                                 static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                                 lse2, lse_in, lse_natural, part, deal ? per : 0, fin);
@@ -992,9 +971,6 @@ static hipError_t stats_launch_rg(const Prob& p, const void* q, const void* k, f
                   s, p, lse2, n);
 }
 
-// Four waves of 32 rows on one key stream.  Two streams of two 64-row waves reuse each
-// key fragment twice per wave but need twice the registers; at one 128-row block (T =
-// 128, LLaVA-NeXT) the one-stream form measured 6 % faster (137-139 against 146-147 us).
 template <int DS, bool HALF, bool COLSUM>
 static hipError_t stats_launch(const Prob& p, const void* q, const void* k, float* lse2,
                                const float* lse_in, int lse_natural, float* part,
@@ -1003,9 +979,9 @@ static hipError_t stats_launch(const Prob& p, const void* q, const void* k, floa
     if constexpr (!COLSUM)
         if (stats_row_blocks((p.max_rows + kTxtRows - 1) / kTxtRows, !p.q_off,
                              (long long)p.B * p.H) == 2)
-            return stats_launch_rg<DS, HALF, COLSUM, 4, 2>(p, q, k, lse2, lse_in, lse_natural, part,
+            return stats_launch_rbw<DS, HALF, COLSUM, 2>(p, q, k, lse2, lse_in, lse_natural, part,
                                                            fin, s);
-    return stats_launch_rg<DS, HALF, COLSUM, 4, 1>(p, q, k, lse2, lse_in, lse_natural, part, fin, s);
+    return stats_launch_rbw<DS, HALF, COLSUM, 1>(p, q, k, lse2, lse_in, lse_natural, part, fin, s);
 }
 
 template <int DS, bool HALF>

@@ -264,7 +264,7 @@ constexpr int kClsPartials = 8192;   // LDS floats of per-chunk partial dot prod
 constexpr int kStatsThreads = 256;
 constexpr int kTxtRows = 128;
 constexpr int kTxtKeysPerWave = 32;
-constexpr int kSelThreads = 256;    // threshold, top-K, budget matching; reference-sum order
+constexpr int kSelThreads = 256;    // threshold; the order of every reference sum
 constexpr int kSelectThreads = 512; // the select kernel (its reference sum uses kSelThreads)
 constexpr int kGatherThreads = 256;
 
@@ -369,8 +369,8 @@ inline bool combine_in_sample(const Prob& p, const ScoreForm& f) {
 }
 
 // Dynamic LDS of the text-row statistics kernel: a ring of kStatsRing key blocks
-// (32 keys x d bf16) per key stream, plus the (max, sum) merge arrays.  Two stages (one
-// block in flight per stream while the other is used) and four workgroups per CU read
+// (32 keys x d bf16), plus the (max, sum) merge arrays.  Two stages (one
+// block in flight while the other is used) and four workgroups per CU read
 // the head slices faster than deeper rings at fewer workgroups per CU: the scattered
 // 256-byte slices stream better with fewer requests outstanding per CU.
 constexpr int kStatsRing = 2;
@@ -405,10 +405,9 @@ inline int stats_splits(long long tasks, long long keys) {
     if (ks > kStatsMaxSplits) ks = kStatsMaxSplits;
     return ks < 1 ? 1 : (int)ks;
 }
-// rg: waves per key stream of one row block (2 or 4); rbw: row blocks per workgroup.
-inline size_t text_stats_smem(int d16, int rg, int rbw = 1) {
-    return (size_t)(kStatsThreads / kWave / rg) * kStatsRing * 32 * d16 * 2 +
-           2 * (size_t)(kStatsThreads / kWave / rg) * rbw * kTxtRows * 4;
+// rbw: row blocks per workgroup.
+inline size_t text_stats_smem(int d16, int rbw) {
+    return (size_t)kStatsRing * 32 * d16 * 2 + 2 * (size_t)rbw * kTxtRows * 4;
 }
 
 // Anchor-path keys per workgroup for a given row geometry.
@@ -588,8 +587,8 @@ hipError_t launch_text_stats(const Prob& p, const void* q, const void* k, float*
 // part [B][ceil(max_rows/128)][H][R + max_cands], then their fixed-order mean.
 hipError_t launch_text_colsum(const Prob& p, const void* q, const void* k, const float* lse,
                               int lse_natural, float* part, float* scores, hipStream_t s);
-// Max-over-rows scoring; with several 128-row blocks, per-block partials go to part
-// [B][ceil(max_rows/128)][R + max_cands] and a combine kernel forms the scores.
+// Max-over-rows scoring; with several row blocks of the form's rows (score_form), per-block
+// partials go to part [B][ceil(max_rows / rows)][R + max_cands] and a combine forms the scores.
 // With fin.done the row-block combine (and with fin.select the threshold and the
 // compaction) run in each sample's last workgroup; without it text_rows_combine follows,
 // unless leave_blocks (launch_select then combines them).
