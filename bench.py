@@ -657,11 +657,11 @@ def fetch_summary(fetch_csv: str, write_csv: str) -> dict:
 # Kernels of one headline step, in launch order: Stage I prune, then Stage II prune (three
 # launches each; the threshold and the compaction run in the scoring kernels).
 STEP_KERNELS = [
-    ("cls_stream_kernel<true, 8, 2>", "cls_stream (Stage I logits + online statistics)"),
-    ("cls_scores_kernel<true>", "cls_scores (Stage I scores, threshold, compaction)"),
+    ("cls_stream_kernel", "cls_stream (Stage I logits + online statistics)"),
+    ("cls_scores_kernel", "cls_scores (Stage I scores, threshold, compaction)"),
     ("pack_gather_kernel", "pack_gather (Stage I: 1024-wide hidden rows)"),
-    ("text_stats_kernel<8, false, false, 4, 1>", "text_stats (Stage II normalisers)"),
-    ("text_score_kernel<8, false, true>", "text_score (Stage II scores, threshold, compaction)"),
+    ("text_stats_kernel", "text_stats (Stage II normalisers)"),
+    ("text_score_kernel", "text_score (Stage II scores, threshold, compaction)"),
     ("pack_gather_kernel", "pack_gather (Stage II: hidden, K and V rows)"),
 ]
 
@@ -680,12 +680,13 @@ def trace_summary(trace_csv: str, warmup: int = 5, steps: int = 20) -> dict:
     import statistics as st
 
     rows = sorted(csv.DictReader(open(trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
-    short = [re.sub(r"\(.*", "", r["Kernel_Name"]).replace("void ", "").replace("occam::", "")
+    # Kernels by their names alone: the template arguments follow the launch rules.
+    short = [re.sub(r"[<(].*", "", r["Kernel_Name"].replace("void ", "")).replace("occam::", "")
              for r in rows]
     dur = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in rows]
     names = [k for k, _ in STEP_KERNELS]
     ours = [i for i, n in enumerate(short) if not n.startswith(("at::", "__amd", "Cijk"))]
-    lone = "text_score_kernel<8, false, true>"
+    lone = "text_score_kernel"
     run, j = [], 0
     while j < len(ours):
         k = j
