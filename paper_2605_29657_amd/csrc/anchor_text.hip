@@ -845,9 +845,9 @@ void text_score_kernel(
     // and each XCD runs one contiguous range of tasks): every workgroup of an XCD walks the
     // heads in the same order, so the chunks of a sample read its query tiles, and the row
     // blocks of a chunk its key slices, at about the same time, and share them in that
-    // XCD's L2.  A start per key chunk instead fetched 1062 MB per launch at the
-    // LLaVA-NeXT shape and 3586 MB on the ragged Qwen3-VL batch; per XCD, 807 and 2654 MB,
-    // ~1 % faster.
+    // XCD's L2: 816 MB fetched per launch at the LLaVA-NeXT shape (790 MB of keys, queries
+    // and scores), 1159 MB on the video batch (1092).  A start per key chunk, measured on 128 x
+    // 128 tasks, fetched 1062 MB where this order fetched 807, ~1 % slower.
     score_task<DS, HALF, NW, NSB, kScoreForms[FORM].keys_lds>(
         p, q, k, lse, lse_natural, scores, part, b, c, rb, (int)blockIdx.x, smem_raw, fin.done != nullptr);
     if (!fin.done) return;
